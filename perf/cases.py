@@ -17,7 +17,8 @@ Inputs are drawn on the GPU from the seed alone. Two scene structures, those of
 the synthetic workloads: ``box`` (means uniform in a box, dense at the
 resolutions used here: long per-tile ranges everywhere) and ``surface`` (means on
 random spheres and planes, strongly uneven tiles: most empty, some with
-thousands of entries).
+thousands of entries). ``shuffled`` stores the surface Gaussians in random order
+(as after densification); otherwise one primitive follows another.
 
 ``exact`` evaluates the image model in binary64 with plain torch: the
 projection, the compositing in (binary32 depth, id) order over per-tile lists,
@@ -39,8 +40,8 @@ KEYS = ("means", "log_scales", "quats", "logits", "sh")
 # cases
 # ---------------------------------------------------------------------------
 
-def _case(kind, scene, n, width, height, degree, tile=16, bins=64, sub=0, **kw):
-    return dict(kind=kind, scene=scene, n=n, width=width, height=height, degree=degree, tile=tile, bins=bins, sub=sub, **kw)
+def _case(kind, scene, n, width, height, degree, tile=16, bins=64, sub=0, shuffled=False, **kw):
+    return dict(kind=kind, scene=scene, n=n, width=width, height=height, degree=degree, tile=tile, bins=bins, sub=sub, shuffled=shuffled, **kw)
 
 
 def listed():
@@ -55,8 +56,8 @@ def listed():
         dict(_case("frame", "surface", 6_000_000, 3840, 2160, 3), name="frame_6m_3840x2160"),
         # the projection layer alone, as a program that keeps splats between calls has it
         dict(_case("project", "surface", 1_000_000, 1920, 1080, 3), name="project_1m_sh3"),
-        # the ordering layer alone at scale: 10M Gaussians, segments of thousands of entries
-        dict(_case("bin", "surface", 10_000_000, 1920, 1080, 0), name="bin_10m_1920x1080"),
+        # the ordering layer alone at scale: 10M Gaussians in random order, segments of thousands of entries
+        dict(_case("bin", "surface", 10_000_000, 1920, 1080, 0, shuffled=True), name="bin_10m_1920x1080"),
         # the raster layer on a uniformly dense scene (the training forward's)
         dict(_case("raster", "box", 500_000, 1297, 840, 0), name="raster_500k_1297x840"),
         # its backward with the tile size and bins that the autotuner picks on such a scene
@@ -80,6 +81,7 @@ def _log_int(rng, lo, hi):
 def draw(rng):
     kind = rng.choice(("frame", "frame", "frame", "project", "bin", "raster", "raster_bwd", "train", "train", "batch"))
     degree = rng.choice((0, 1, 2, 3, 3))
+    shuffled = rng.random() < 0.5
     # 16-pixel tiles with 64 bins are the default; the others are what the autotuner chooses from
     tile, bins, sub = rng.choice(((16, 64, 0), (16, 64, 0), (16, 64, 0), (16, 128, 4), (8, 32, 0), (32, 128, 2)))
     if kind == "batch":
@@ -92,19 +94,19 @@ def draw(rng):
     if kind == "frame":
         scene = rng.choice(("surface", "surface", "box"))
         n = _log_int(rng, 2000, 4_000_000 if scene == "surface" else 500_000)
-        return _case(kind, scene, n, width, height, degree, tile, bins, sub)
+        return _case(kind, scene, n, width, height, degree, tile, bins, sub, shuffled)
     if kind == "project":
-        return _case(kind, rng.choice(("surface", "box")), _log_int(rng, 5000, 4_000_000), width, height, degree, tile, bins, sub)
+        return _case(kind, rng.choice(("surface", "box")), _log_int(rng, 5000, 4_000_000), width, height, degree, tile, bins, sub, shuffled)
     if kind == "bin":
         width, height = min(width, 1920), min(height, 1080)
-        return _case(kind, "surface", _log_int(rng, 20_000, 10_000_000), width, height, 0, tile, bins, sub)
+        return _case(kind, "surface", _log_int(rng, 20_000, 10_000_000), width, height, 0, tile, bins, sub, shuffled)
     width = _log_int(rng, 160, 1600)
     height = max(96, min(1080, int(width * rng.uniform(0.5, 1.0))))
     n = _log_int(rng, 5000, 500_000)
     scene = rng.choice(("box", "box", "surface"))
     if kind == "train":
-        return _case(kind, scene, n, width, height, degree, tile, bins, sub)
-    return _case(kind, scene, n, width, height, 0, tile, bins, sub)
+        return _case(kind, scene, n, width, height, degree, tile, bins, sub, shuffled)
+    return _case(kind, scene, n, width, height, 0, tile, bins, sub, shuffled)
 
 
 # ---------------------------------------------------------------------------
@@ -133,7 +135,8 @@ def _gaussians(case, seed):
         logit_std = 1.5
     else:
         prims = 64
-        k = torch.arange(n, device="cuda") % prims
+        k = torch.arange(n, device="cuda")
+        k = k % prims if case["shuffled"] else k * prims // n
         centres = _uniform(gen, -4.0, 4.0, prims, 3)
         radii, sides = _uniform(gen, 0.5, 2.0, prims), _uniform(gen, 1.0, 4.0, prims)
         frame = torch.linalg.qr(torch.randn(prims, 3, 3, generator=gen, device="cuda"))[0]
