@@ -367,14 +367,13 @@ TGS_API tgs_status tgs_project_backward(const tgs_gaussians* gaussians, const tg
 
 /* Batched rendering: up to TGS_MAX_VIEWS cameras (views), each with its own
    projected splats, tgs_bin stream (any order, tile size and bin counts of
-   its params), composited in ONE persistent launch. Work items are (view,
-   tile, 8x8 block), ordered heaviest tile first over all views and pulled
-   by wavefronts from device-scope cursors until none is left; each item is
-   the WAVE raster's block walk, so every view's rgb / alpha / last are
-   bit-identical to tgs_rasterize with that view's arguments. All host
+   its params), composited in ONE launch. Work items are (view, tile, 8x8
+   block), ordered heaviest tile first over all views, one wavefront each;
+   each item is the WAVE raster's block walk, so every view's rgb / alpha /
+   last are bit-identical to tgs_rasterize with that view's arguments. All host
    arrays have num_views elements; rgb / alpha / last are host arrays of
    device pointers. The call enqueues a fill, two small ordering launches
-   and the persistent launch on `stream` and never synchronises, so it can
+   and the raster launch on `stream` and never synchronises, so it can
    be captured in a HIP graph (the view descriptors travel in the kernel
    arguments). Workspace: tgs_batch_workspace_size bytes, caller-owned. */
 TGS_API size_t tgs_batch_workspace_size(int32_t num_views, const tgs_camera* cameras, const tgs_params* params);

@@ -354,7 +354,7 @@ class BatchRenderer:
     """Several cameras per frame: tgs_project_views for all views (the
     Gaussians read once per eight views), per-view tgs_bin (BINNED, each view
     with its own params: tile size, bins; up to ``lanes`` views at once on
-    side streams), then one tgs_rasterize_batch persistent launch for all
+    side streams), then one tgs_rasterize_batch raster launch for all
     views. ``capture`` records
     the whole frame in a HIP graph (torch.cuda.CUDAGraph) after an eager
     frame has sized every buffer; ``replay`` launches it."""

@@ -2,7 +2,7 @@
 
 For one camera and scene size it times the whole per-view frame as the
 batched renderer runs it (projection, binning with exact repair, the
-persistent multi-view raster on this one view) for every candidate (tile
+batched multi-view raster on this one view) for every candidate (tile
 size in {8, 16, 32}) x (bins K in {16, 32, 64, 128, 256}) x (sub-bins per bin in
 {8, 4, 2}) with HIP events on the launch stream and keeps the fastest. The
 choice never changes the image beyond rounding (exact repair keeps the
@@ -38,7 +38,7 @@ def cache_key(cam, n):
 
 
 def measure(g, cam, tile_size, num_bins, reps=5, warmup=2, sub_bins=0):
-    """Median ms of one view's frame (project + bin + the persistent batched
+    """Median ms of one view's frame (project + bin + the batched
     raster on this view alone) with these options, inputs resident."""
     p = Params(tile_size=tile_size, num_bins=num_bins, sub_bins=sub_bins)
     br = BatchRenderer([cam], [p], device=g["means"].device)

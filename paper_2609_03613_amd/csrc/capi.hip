@@ -638,26 +638,10 @@ namespace {
 constexpr int kMaxDevices = 64;
 std::mutex g_dev_mu;
 void* g_scratch_dev[kMaxDevices] = {};  // device address of `scratch`, per device
-int g_batch_grid[kMaxDevices] = {};     // persistent-raster workgroups, per device
 
 tgs_status current_device(int* dev) {
     TGS_HIP(hipGetDevice(dev), "current device");
     if (*dev < 0 || *dev >= kMaxDevices) return fail(TGS_ERR_UNSUPPORTED, "device index %d >= %d", *dev, kMaxDevices);
-    return TGS_OK;
-}
-
-// Workgroups of the persistent raster on the current device: 8 per CU.
-tgs_status batch_grid(int* grid) {
-    int dev = 0;
-    tgs_status st = current_device(&dev);
-    if (st) return st;
-    std::lock_guard<std::mutex> lk(g_dev_mu);
-    if (g_batch_grid[dev] == 0) {
-        int cus = 0;
-        TGS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "device attributes");
-        g_batch_grid[dev] = (cus > 0 ? cus : 1) * 8;
-    }
-    *grid = g_batch_grid[dev];
     return TGS_OK;
 }
 
@@ -737,18 +721,12 @@ tgs_status batch_args(int32_t num_views, const tgs_projected* pr, const tgs_binn
 
 // Enqueues the batched raster with its control words and work list in ws
 // (at least tgs_batch_workspace_size bytes, 256-byte aligned): a fill kernel
-// clears the control words, then the two ordering launches and the
-// persistent launch.
+// clears the control words, then the two ordering launches and the walk.
 tgs_status batch_launch(const BatchArgs& a, int64_t blocks, void* ws, void* stream) {
-    int grid = 0;
-    tgs_status st = batch_grid(&grid);
-    if (st) return st;
-    const int64_t want = (blocks + 3) / 4;
-    const int g = (int)(want < grid ? want : grid);
     hipStream_t s = (hipStream_t)stream;
     uint32_t* ctl = (uint32_t*)ws;
     TGS_HIP(launch_fill_u32(ctl, 0u, 256, s), "clear batch control words");
-    TGS_HIP(launch_raster_batch(a, ctl, ctl + 256, blocks, g > 0 ? g : 1, s), "batched raster");
+    TGS_HIP(launch_raster_batch(a, ctl, ctl + 256, blocks, s), "batched raster");
     return TGS_OK;
 }
 

@@ -492,7 +492,7 @@ struct RasterArgs {
 hipError_t launch_raster_plain(const RasterArgs& a, hipStream_t s);
 hipError_t launch_raster_wave(const RasterArgs& a, hipStream_t s);
 
-// Batched persistent raster: up to kMaxViews views in one launch (passed by
+// Batched raster: up to kMaxViews views in one launch (passed by
 // value as the kernel argument, so a captured graph keeps them).
 constexpr int kMaxViews = 16;
 struct BatchView {
@@ -523,8 +523,8 @@ size_t mlp_train_workspace_floats(int64_t T);
 hipError_t launch_mlp_train_step(float* w, float* v, const float* feat, const float* regret, int64_t T, float lr,
                                  float mu, float* ws, float* loss, hipStream_t s);
 
-// ctl: 256 zeroed words; work: 8 * ceil(total_blocks / 8) words.
-hipError_t launch_raster_batch(const BatchArgs& b, uint32_t* ctl, uint32_t* work, int64_t total_blocks, int grid,
+// ctl: 256 zeroed words; work: total_blocks words.
+hipError_t launch_raster_batch(const BatchArgs& b, uint32_t* ctl, uint32_t* work, int64_t total_blocks,
                                hipStream_t s);
 
 // Gradient lines: 12 floats per Gaussian (dL/d mean_x, mean_y, conic a, b,

@@ -1,5 +1,5 @@
 // Per-pixel compositing step, entry staging and the 8x8-block walk shared by
-// the forward rasters, the batched persistent raster and the backward raster
+// the forward rasters, the batched raster and the backward raster
 // (device code, included by the raster sources only).
 #pragma once
 
