@@ -310,7 +310,8 @@ int64_t scan_blocks(int64_t n);
 // buffers). ticket and status_x / status_y [scan_blocks(n)] must be zero.
 hipError_t launch_emit_scan(const uint32_t* info, int64_t n, int tiles_x, int tiles_y, uint32_t* emit_off,
                             uint32_t* vis_ids, uint32_t* ticket, uint64_t* status_x, uint64_t* status_y,
-                            int64_t* counters, int64_t capacity, hipStream_t s);
+                            int64_t* counters, int64_t capacity,
+                            int64_t* count_host, hipStream_t s);
 
 // Depth samples: the visible Gaussians at ranks floor(i V / S), i < S (all
 // of them when V <= S), read through vis_ids; samples [S] is scratch for

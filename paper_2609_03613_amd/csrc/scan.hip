@@ -172,7 +172,8 @@ __device__ __forceinline__ uint64_t block_excl_u64(uint64_t v, uint64_t* lds, ui
 // ---- entry-emission scan ---------------------------------------------------
 // Per Gaussian: x = number of tiles (entries), y = 1 if visible. Writes
 // emit_off[g] (exclusive prefix of x), vis_ids[rank] = g for visible g, and
-// counters[0] = M, counters[1] = V, counters[2] = M > capacity.
+// counters[0] = M, counters[1] = V, counters[2] = M > capacity. count_host
+// (host memory the device can write, or null) = M.
 // Items are loaded and stored in coalesced rounds; in between they pass
 // through LDS so that each thread scans kEmitRounds consecutive items and one
 // workgroup scan of the packed pair (x << 24 | y; y <= kEmitPerBlock) serves
@@ -182,7 +183,8 @@ __global__ void __launch_bounds__(kEmitThreads) emit_scan_kernel(const uint4* __
                                                              int tiles_y, uint32_t* __restrict__ emit_off,
                                                              uint32_t* __restrict__ vis_ids, uint32_t* ticket,
                                                              uint64_t* status_x, uint64_t* status_y,
-                                                             int64_t* __restrict__ counters, int64_t capacity) {
+                                                             int64_t* __restrict__ counters, int64_t capacity,
+                                                             int64_t* count_host) {
     static_assert(kEmitRounds % 4 == 0 && kEmitPerBlock < (1 << 24), "packed pair layout");
     __shared__ uint32_t tk;
     __shared__ __align__(16) uint32_t item_x[kEmitPerBlock];  // tile counts, then exclusive x
@@ -247,6 +249,7 @@ __global__ void __launch_bounds__(kEmitThreads) emit_scan_kernel(const uint4* __
     const uint32_t cy = (uint32_t)pre[1];
     if (b == nb - 1 && threadIdx.x == 0) {
         counters[0] = (int64_t)(cx + ax);
+        if (count_host) __hip_atomic_store(count_host, (int64_t)(cx + ax), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         counters[1] = (int64_t)(cy + ay);
         counters[2] = (int64_t)(cx + ax) > capacity ? 1 : 0;
         counters[3] = 0;
@@ -938,11 +941,11 @@ int64_t scan_blocks(int64_t n) { return n > 0 ? (n + kPerBlock - 1) / kPerBlock 
 
 hipError_t launch_emit_scan(const uint32_t* info, int64_t n, int tiles_x, int tiles_y, uint32_t* emit_off,
                             uint32_t* vis_ids, uint32_t* ticket, uint64_t* status_x, uint64_t* status_y,
-                            int64_t* counters, int64_t capacity, hipStream_t s) {
+                            int64_t* counters, int64_t capacity, int64_t* count_host, hipStream_t s) {
     const int64_t blocks = n > 0 ? (n + kEmitPerBlock - 1) / kEmitPerBlock : 1;
     hipLaunchKernelGGL(emit_scan_kernel, dim3((unsigned)blocks), dim3(kEmitThreads), 0, s,
                        reinterpret_cast<const uint4*>(info), n, tiles_x, tiles_y, emit_off, vis_ids, ticket, status_x,
-                       status_y, counters, capacity);
+                       status_y, counters, capacity, count_host);
     return hipGetLastError();
 }
 
