@@ -518,9 +518,14 @@ __global__ void __launch_bounds__(kScatterThreads) group_scatter_kernel(const ui
                                                             const uint32_t* __restrict__ group_off,
                                                             const uint32_t* __restrict__ wgbase,
                                                             uint64_t* __restrict__ tmp_pair,
-                                                            uint16_t* __restrict__ tmp_code, int64_t capacity) {
+                                                            uint16_t* __restrict__ tmp_code, int64_t capacity,
+                                                            GroupSplit sp) {
     constexpr int NT = kScatterThreads, NW = NT / kWave;
     static_assert(kGroupChunk % NT == 0, "whole wavefront slabs per chunk");
+    if (sp.list) {
+        const int64_t words = (int64_t)sp.ctl[0] * sp.stride;
+        for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < words; i += (int64_t)gridDim.x * NT) sp.hist[i] = 0;
+    }
     __shared__ WaveGauss wg[NW];
     __shared__ uint32_t cursor[kMaxGroups];
     const uint32_t* row = wgbase + (int64_t)blockIdx.x * gm.G;
@@ -628,29 +633,24 @@ __device__ __forceinline__ void sort_groups(const SmallSort& S, int b, uint32_t 
     }
 }
 
+// cnt: entries per bucket
 template <bool DESC>
-__global__ void __launch_bounds__(256) sort_small_kernel(const uint32_t* __restrict__ bin_off,
-                                                         const uint32_t* __restrict__ lists, int64_t nseg,
-                                                         const uint32_t* __restrict__ bucket_count,
-                                                         uint64_t* __restrict__ pairs, RecordSink rs) {
-    const SmallSort S{bin_off, lists, nseg, pairs, gridDim.x * (blockDim.x / kWave),
-                      blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave};
-    const uint32_t c0 = bucket_count[0], c1 = bucket_count[1], c2 = bucket_count[2], c3 = bucket_count[3],
-                   c4 = bucket_count[4];
+__device__ __forceinline__ void sort_small(const SmallSort& S, const uint32_t (&cnt)[5], const RecordSink& rs) {
+    const uint32_t c0 = cnt[0], c1 = cnt[1], c2 = cnt[2], c3 = cnt[3], c4 = cnt[4];
     // job counts and their running sums, bucket 4 first
     const uint32_t j4 = c4, j3 = j4 + c3, j2 = j3 + (c2 + 1) / 2, j1 = j2 + (c1 + 3) / 4, j0 = j1 + (c0 + 7) / 8;
     if (S.wid >= j0) return;
     for (uint32_t j = first_job(S, 0); j < j4; j += S.waves) {
         uint32_t sg = 0, begin = 0, len = 0;
-        const int64_t at = (int64_t)4 * nseg + j;
-        locate<DESC>(bin_off, DESC ? reinterpret_cast<const uint2*>(lists)[at] : make_uint2(lists[at], 0u), sg,
+        const int64_t at = (int64_t)4 * S.nseg + j;
+        locate<DESC>(S.bin_off, DESC ? reinterpret_cast<const uint2*>(S.lists)[at] : make_uint2(S.lists[at], 0u), sg,
                      begin, len);
         if (len <= 2 * kWave)
-            sort_wave_reg<2, !DESC>(pairs + begin, sg, begin, len, rs);
+            sort_wave_reg<2, !DESC>(S.pairs + begin, sg, begin, len, rs);
         else if (len <= 4 * kWave)
-            sort_wave_reg<4, !DESC>(pairs + begin, sg, begin, len, rs);
+            sort_wave_reg<4, !DESC>(S.pairs + begin, sg, begin, len, rs);
         else
-            sort_wave_reg<8, !DESC>(pairs + begin, sg, begin, len, rs);
+            sort_wave_reg<8, !DESC>(S.pairs + begin, sg, begin, len, rs);
     }
     sort_groups<64, DESC>(S, 3, j4, j3, c3, rs);
     sort_groups<32, DESC>(S, 2, j3, j2, c2, rs);
@@ -658,30 +658,146 @@ __global__ void __launch_bounds__(256) sort_small_kernel(const uint32_t* __restr
     sort_groups<8, DESC>(S, 0, j1, j0, c0, rs);
 }
 
-// Buckets 5..7: one workgroup per segment. 513..8192 keys: bitonic network
-// in LDS over the next power of two, padded with the maximum key. Above
+// The parts of the split groups (GroupSplit), one per workgroup, sorted in
+// place: bucket sort by tile and depth over the part's own depth range. A
+// bucket of up to kBucketRank pairs is ordered by rank; longer ones (depths
+// far more clustered than the range) are queued for the long-segment launch,
+// as is a part longer than the stage (a single code). The next part's entries
+// are in flight while one is written out.
+constexpr int kPartThreads = 1024;
+constexpr int kPartGrid = 512;          // two workgroups per CU: all its wavefronts
+constexpr int kPartCap = 2 * kPartLen;  // keys of the bucket sort
+using PartLds = BucketLds<kPartThreads, kPartCap>;
+__device__ __forceinline__ void sort_parts(uint64_t* __restrict__ pairs, const uint16_t* __restrict__ part_tile,
+                                           uint2* __restrict__ lists, int64_t list_stride,
+                                           uint32_t* __restrict__ bucket_count, const GroupSplit& sp, PartLds& L) {
+    constexpr int NT = kPartThreads, kEnt = kPartCap / NT;
+    static_assert(kBucketSlots >= kMaxGroupSegs, "a bucket per tile");
+    static_assert(kBucketRank >= 512, "only buckets 5..7 are queued");
+    auto queue = [&](uint32_t begin, uint32_t len) {
+        const int k = bucket_of(len);
+        lists[(int64_t)k * list_stride + atomicAdd(&bucket_count[k], 1u)] = make_uint2(begin, len);
+    };
+    const uint32_t units = sp.ctl[2];
+    uint64_t pr[kEnt];
+    uint32_t b[kEnt];
+    uint4 u = make_uint4(0u, 0u, 0u, 1u);
+    auto load = [&](uint32_t it) {
+        u = it < units ? sp.units[it] : make_uint4(0u, 0u, 0u, 1u);
+        if (u.y < 2 || u.y > (uint32_t)kPartCap) return;
+#pragma unroll
+        for (int j = 0; j < kEnt; ++j) {
+            const uint32_t e = u.x + min((uint32_t)(j * NT) + threadIdx.x, u.y - 1);
+            pr[j] = pairs[e];
+            b[j] = u.w == 1 ? u.z : (uint32_t)part_tile[e];
+        }
+    };
+    load(blockIdx.x);
+    for (uint32_t it = blockIdx.x; it < units; it += gridDim.x) {
+        const uint32_t lo = u.x, n = u.y;
+        if (n < 2 || n > (uint32_t)kPartCap) {
+            if (n >= 2 && threadIdx.x == 0) queue(lo, n);
+            load(it + gridDim.x);
+            continue;
+        }
+#pragma unroll
+        for (int j = 0; j < kEnt; ++j) b[j] -= u.z;
+        range_buckets(pr, b, u.w, L);
+        const bool clustered = place_buckets(pr, b, n, L);
+        load(it + gridDim.x);
+        for (uint32_t q = threadIdx.x; q < n; q += NT) {
+            const uint32_t k = L.bucket[q], at = L.off[k], len = L.off[k + 1] - at;
+            const uint64_t v = L.stage[q];
+            pairs[lo + (len >= 2 && len <= (uint32_t)kBucketRank ? rank_slot(L.stage, v, at, len) : q)] = v;
+        }
+        if (clustered)
+            for (int k = threadIdx.x; k < kBucketSlots; k += NT) {
+                const uint32_t at = L.off[k], len = L.off[k + 1] - at;
+                if (len > (uint32_t)kBucketRank) queue(lo + at, len);
+            }
+        __syncthreads();
+    }
+}
+
+// The parts (PARTS) and then the short segments: neither depends on the other,
+// and a launch of its own would cost the parts 5 us where there are none.
+template <bool DESC, bool PARTS>
+__global__ void __launch_bounds__(PARTS ? kPartThreads : 256, PARTS ? 8 : 1)
+    sort_small_kernel(const uint32_t* __restrict__ bin_off, uint32_t* __restrict__ lists, int64_t nseg,
+                      uint32_t* __restrict__ bucket_count, uint64_t* __restrict__ pairs, RecordSink rs, GroupSplit sp,
+                      const uint16_t* __restrict__ part_tile) {
+    static_assert(DESC || !PARTS, "parts are queued as descriptors");
+    const uint32_t cnt[5] = {bucket_count[0], bucket_count[1], bucket_count[2], bucket_count[3], bucket_count[4]};
+    if constexpr (PARTS) {
+        __shared__ PartLds L;
+        sort_parts(pairs, part_tile, reinterpret_cast<uint2*>(lists), nseg, bucket_count, sp, L);
+    }
+    constexpr uint32_t NW = (PARTS ? kPartThreads : 256) / kWave;
+    const SmallSort S{bin_off, lists, nseg, pairs, gridDim.x * NW, blockIdx.x * NW + threadIdx.x / kWave};
+    sort_small<DESC>(S, cnt, rs);
+}
+
+// Buckets 5..7: one workgroup per segment. 513..8192 keys: in LDS. Above
 // 8192: in place in global memory, with the network in the form whose every
 // comparator puts the smaller key at the lower index (each merge starts by
 // comparing mirrored positions), so positions at or beyond the segment
 // length act as +infinity and are never touched.
 constexpr int kLargeThreads = 512;
 constexpr int kLargeCap = 8192;
+constexpr int kLargeGrid = 256;  // one workgroup per CU (LDS)
 
 constexpr int kOrderBuckets = 33;  // tile order buckets: bit lengths 32 .. 0 of the entry count
+struct PlaceLds {
+    uint32_t h[kOrderBuckets], base[kOrderBuckets], all[kOrderBuckets];
+    uint32_t copies[kOrderBuckets][32];  // histogram copies, one per LDS bank
+};
 template <int NT>
-__device__ __forceinline__ void tile_place_chunk(const TileOrder& to, int64_t chunk, uint32_t* h, uint32_t* base);
+__device__ __forceinline__ void tile_hist_all(const TileOrder& to, PlaceLds& L);
+template <int NT>
+__device__ __forceinline__ void tile_place_chunk(const TileOrder& to, int64_t chunk, PlaceLds& L);
 
-// One segment of 513..8192 keys by the workgroup: coalesced load into LDS
-// (padded slots), E keys per thread into registers, the register / lane /
-// LDS bitonic network of sort_block_reg, and a coalesced store (with the
-// records when !DESC).
+// LDS of the long-segment sorts: block_slot<E> of P = 512 E keys for the
+// network (at most 8192 + 512), or the bucket sort's.
+union LargeLds {
+    uint64_t net[kLargeCap + kLargeThreads];
+    BucketLds<kLargeThreads, kLargeCap> buckets;
+    PlaceLds place;
+};
+
+// One segment of 513..8192 keys by the workgroup, E keys per thread: bucket
+// sort over the segment's own depth range, or, when some depths are too
+// clustered for it, the register / lane / LDS bitonic network of
+// sort_block_reg; coalesced loads and stores (with the records when !DESC).
+// The network makes 91 compare steps over 8192 keys, the bucket sort a few LDS
+// accesses per key: with a longest segment of 4295 keys (10 million Gaussians
+// on 1920x1080) this launch took 249 us, now 37.
 template <int E, bool DESC>
 __device__ __forceinline__ void sort_large_block(uint64_t* pairs, uint32_t s, uint32_t begin, uint32_t len,
-                                                 const RecordSink& rs, uint64_t* buf) {
+                                                 const RecordSink& rs, LargeLds& lds) {
     constexpr uint32_t P = (uint32_t)kLargeThreads * E;
+    uint64_t v[E];
+    {
+        uint32_t b[E] = {};
+#pragma unroll
+        for (int j = 0; j < E; ++j) v[j] = pairs[begin + min((uint32_t)(j * kLargeThreads) + threadIdx.x, len - 1)];
+        BucketLds<kLargeThreads, kLargeCap>& L = lds.buckets;
+        range_buckets(v, b, 1u, L);
+        if (!place_buckets(v, b, len, L)) {
+            for (uint32_t q = threadIdx.x; q < len; q += kLargeThreads) {
+                const uint32_t k = L.bucket[q], at = L.off[k], n = L.off[k + 1] - at;
+                const uint64_t x = L.stage[q];
+                const uint32_t to = begin + (n >= 2 ? rank_slot(L.stage, x, at, n) : q);
+                pairs[to] = x;
+                if (!DESC) rs.put(s, to, x);
+            }
+            __syncthreads();
+            return;
+        }
+        __syncthreads();
+    }
+    uint64_t* buf = lds.net;
     for (uint32_t e = threadIdx.x; e < P; e += kLargeThreads) buf[block_slot<E>(e)] = e < len ? pairs[begin + e] : ~0ull;
     __syncthreads();
-    uint64_t v[E];
 #pragma unroll
     for (int k = 0; k < E; ++k) v[k] = buf[block_slot<E>((uint32_t)(threadIdx.x * E + k))];
     __syncthreads();
@@ -698,45 +814,42 @@ __device__ __forceinline__ void sort_large_block(uint64_t* pairs, uint32_t s, ui
 }
 
 template <bool DESC>
-__global__ void __launch_bounds__(kLargeThreads) sort_large_kernel(const uint32_t* __restrict__ bin_off,
-                                                                   const uint32_t* __restrict__ lists, int64_t nseg,
-                                                                   const uint32_t* __restrict__ bucket_count,
-                                                                   uint64_t* pairs, RecordSink rs, TileOrder to) {
-    __shared__ uint64_t buf[kLargeCap + kLargeThreads];  // block_slot<E> of P = 512 E keys: at most 8192 + 512
-    auto entry = [&](int bucket, uint32_t i) {
-        const int64_t at = (int64_t)bucket * nseg + i;
-        return DESC ? reinterpret_cast<const uint2*>(lists)[at] : make_uint2(lists[at], 0u);
-    };
-    for (int bucket = 5; bucket <= 6; ++bucket) {
-        const uint32_t cnt = bucket_count[bucket];
-        for (uint32_t i = blockIdx.x; i < cnt; i += gridDim.x) {
-            uint32_t s, begin, len;
-            locate<DESC>(bin_off, entry(bucket, i), s, begin, len);
-            uint32_t P = 1;
-            while (P < len) P <<= 1;
-            // E = P / kLargeThreads keys per thread (P = 1024 .. 8192)
-            if (P <= 1024)
-                sort_large_block<2, DESC>(pairs, s, begin, len, rs, buf);
-            else if (P <= 2048)
-                sort_large_block<4, DESC>(pairs, s, begin, len, rs, buf);
-            else if (P <= 4096)
-                sort_large_block<8, DESC>(pairs, s, begin, len, rs, buf);
-            else
-                sort_large_block<16, DESC>(pairs, s, begin, len, rs, buf);
+__device__ __forceinline__ void sort_large(uint64_t* pairs, uint32_t s, uint32_t begin, uint32_t len,
+                                           const RecordSink& rs, LargeLds& lds) {
+    if (len <= 1024)
+        sort_large_block<2, DESC>(pairs, s, begin, len, rs, lds);
+    else if (len <= 2048)
+        sort_large_block<4, DESC>(pairs, s, begin, len, rs, lds);
+    else if (len <= 4096)
+        sort_large_block<8, DESC>(pairs, s, begin, len, rs, lds);
+    else
+        sort_large_block<16, DESC>(pairs, s, begin, len, rs, lds);
+}
+
+// A segment of more than 8192 keys, in global memory.
+template <bool DESC>
+__device__ __forceinline__ void sort_global(uint64_t* pairs, uint32_t s, uint32_t begin, uint32_t len,
+                                            const RecordSink& rs) {
+    uint64_t* a = pairs + begin;
+    uint32_t P = 1;
+    while (P < len) P <<= 1;
+    for (uint32_t k = 2; k <= P; k <<= 1) {
+        const uint32_t h = k >> 1;
+        for (uint32_t t = threadIdx.x; t < P / 2; t += kLargeThreads) {
+            const uint32_t blk = t / h, off = t % h;
+            const uint32_t lo = blk * k + off, hi = blk * k + k - 1 - off;
+            if (hi < len) {
+                const uint64_t x = a[lo], y = a[hi];
+                if (x > y) {
+                    a[lo] = y;
+                    a[hi] = x;
+                }
+            }
         }
-    }
-    const uint32_t cnt = bucket_count[7];
-    for (uint32_t i = blockIdx.x; i < cnt; i += gridDim.x) {
-        uint32_t s, begin, len;
-        locate<DESC>(bin_off, entry(7, i), s, begin, len);
-        uint64_t* a = pairs + begin;
-        uint32_t P = 1;
-        while (P < len) P <<= 1;
-        for (uint32_t k = 2; k <= P; k <<= 1) {
-            const uint32_t h = k >> 1;
+        __syncthreads();
+        for (uint32_t j = k >> 2; j > 0; j >>= 1) {
             for (uint32_t t = threadIdx.x; t < P / 2; t += kLargeThreads) {
-                const uint32_t blk = t / h, off = t % h;
-                const uint32_t lo = blk * k + off, hi = blk * k + k - 1 - off;
+                const uint32_t lo = (t / j) * 2 * j + (t % j), hi = lo + j;
                 if (hi < len) {
                     const uint64_t x = a[lo], y = a[hi];
                     if (x > y) {
@@ -746,31 +859,54 @@ __global__ void __launch_bounds__(kLargeThreads) sort_large_kernel(const uint32_
                 }
             }
             __syncthreads();
-            for (uint32_t j = k >> 2; j > 0; j >>= 1) {
-                for (uint32_t t = threadIdx.x; t < P / 2; t += kLargeThreads) {
-                    const uint32_t lo = (t / j) * 2 * j + (t % j), hi = lo + j;
-                    if (hi < len) {
-                        const uint64_t x = a[lo], y = a[hi];
-                        if (x > y) {
-                            a[lo] = y;
-                            a[hi] = x;
-                        }
-                    }
-                }
-                __syncthreads();
-            }
         }
-        if (!DESC)
-            for (uint32_t e = threadIdx.x; e < len; e += kLargeThreads) rs.put(s, begin + e, a[e]);
-        __syncthreads();
+    }
+    if (!DESC)
+        for (uint32_t e = threadIdx.x; e < len; e += kLargeThreads) rs.put(s, begin + e, a[e]);
+    __syncthreads();
+}
+
+template <bool DESC>
+__global__ void __launch_bounds__(kLargeThreads) sort_large_kernel(const uint32_t* __restrict__ bin_off,
+                                                                   const uint32_t* __restrict__ lists, int64_t nseg,
+                                                                   const uint32_t* __restrict__ bucket_count,
+                                                                   uint64_t* pairs, RecordSink rs, TileOrder to,
+                                                                   RepairSum sum) {
+    __shared__ LargeLds lds;
+    const uint32_t counts[3] = {bucket_count[5], bucket_count[6], bucket_count[7]};
+    for (int bucket = 5; bucket <= 7; ++bucket) {
+        for (uint32_t i = blockIdx.x; i < counts[bucket - 5]; i += gridDim.x) {
+            const int64_t at = (int64_t)bucket * nseg + i;
+            uint32_t s, begin, len;
+            locate<DESC>(bin_off, DESC ? reinterpret_cast<const uint2*>(lists)[at] : make_uint2(lists[at], 0u), s,
+                         begin, len);
+            if (bucket < 7)
+                sort_large<DESC>(pairs, s, begin, len, rs, lds);
+            else
+                sort_global<DESC>(pairs, s, begin, len, rs);
+        }
     }
     // the tile order's placement, by the last workgroups (the first ones
     // take the long segments)
+    const int64_t c0 = (int64_t)gridDim.x - 1 - blockIdx.x;
     if (to.order) {
-        __shared__ uint32_t oh[kOrderBuckets], ob[kOrderBuckets];
         const int64_t chunks = (to.T + kLargeThreads - 1) / kLargeThreads;
-        for (int64_t c = (int64_t)gridDim.x - 1 - blockIdx.x; c < chunks; c += gridDim.x)
-            tile_place_chunk<kLargeThreads>(to, c, oh, ob);
+        if (c0 < chunks && to.counts) tile_hist_all<kLargeThreads>(to, lds.place);
+        for (int64_t c = c0; c < chunks; c += gridDim.x) tile_place_chunk<kLargeThreads>(to, c, lds.place);
+    }
+    if (sum.queued && blockIdx.x == 0) {
+        constexpr int NW = kLargeThreads / kWave;
+        __shared__ uint64_t part[NW];
+        uint64_t s = 0;
+        for (int g = threadIdx.x; g < sum.G; g += kLargeThreads) s += sum.queued[g];
+#pragma unroll
+        for (int m = 1; m < kWave; m <<= 1) s += shfl_xor_u64(s, m);
+        if (lane() == 0) part[threadIdx.x / kWave] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < NW; ++w) s += part[w];
+            sum.counters[3] = (int64_t)s;
+        }
     }
 }
 
@@ -818,69 +954,98 @@ __global__ void __launch_bounds__(256) tile_hist_kernel(const uint32_t* __restri
     if (threadIdx.x < kOrderBuckets && h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
 }
 
-// Placement of tiles [chunk NT, chunk NT + NT) by a workgroup of NT
-// threads; h, base: LDS [kOrderBuckets]. Ends with a barrier.
+// The histogram of all tiles' buckets from their counts, by one workgroup
+// (a copy per bank: most tiles share a few buckets).
 template <int NT>
-__device__ __forceinline__ void tile_place_chunk(const TileOrder& to, int64_t chunk, uint32_t* h, uint32_t* base) {
-    const uint32_t* hist = to.hist;
-    uint32_t* cursor = to.hist + kOrderBuckets;
-    const int64_t T = to.T;
-    if (threadIdx.x < kOrderBuckets) h[threadIdx.x] = 0;
+__device__ __forceinline__ void tile_hist_all(const TileOrder& to, PlaceLds& L) {
+    for (int i = threadIdx.x; i < kOrderBuckets * 32; i += NT) (&L.copies[0][0])[i] = 0;
     __syncthreads();
-    const int64_t t = chunk * NT + threadIdx.x;
-    const bool act = t < T;
-    const int b = act ? order_bucket(tile_count(to.offsets, to.sm, t)) : 0;
-    const uint32_t slot = wave_aggregated_add(h, b, act);
-    __syncthreads();
-    if (threadIdx.x < kOrderBuckets) {
-        uint32_t start = 0;
-        for (int k = 0; k < (int)threadIdx.x; ++k) start += hist[k];
-        base[threadIdx.x] = h[threadIdx.x] ? start + atomicAdd(&cursor[threadIdx.x], h[threadIdx.x]) : 0u;
+    constexpr int kAhead = 4;
+    for (int64_t t0 = 0; t0 < to.T; t0 += kAhead * NT) {
+        uint32_t c[kAhead];
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            const int64_t t = t0 + j * NT + threadIdx.x;
+            c[j] = to.counts[t < to.T ? t : to.T - 1];
+        }
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j)
+            if (t0 + j * NT + threadIdx.x < to.T) atomicAdd(&L.copies[order_bucket(c[j])][threadIdx.x & 31], 1u);
     }
     __syncthreads();
-    if (act) to.order[base[b] + slot] = (uint32_t)t;
-    if (chunk == 0 && threadIdx.x == 0) {
-        // counts >= 2^h have a bit length > h: buckets 0 .. 31 - h. The
-        // threshold is the smallest power of two >= split and >= `factor`
-        // times the mean count of the non-empty tiles that leaves at most
-        // kSplitTiles tiles above it, so the split set is a union of whole
-        // buckets (independent of the order inside a bucket). Only tiles
-        // far longer than the typical walk are on the critical path, and
-        // only when the longest reach at least twice that bound (a long
-        // tail): where every tile is long the quad walk's extra
-        // instructions per entry cost more than its shorter walks gain.
-        uint32_t nh = 0, thr = 0;
-        if (to.split > 0) {
-            const uint64_t m = to.offsets[to.sm.first(T)];
-            const uint64_t nonempty = (uint64_t)T - hist[32];
-            // with fewer block wavefronts than the CUs hold (256 x 32), the
-            // quad walks run on otherwise idle SIMDs: no bound from the mean
-            const bool filled = 4 * nonempty >= (uint64_t)kFillWaves;
-            const uint64_t rel = nonempty && filled ? (uint64_t)to.factor * m / nonempty : 0;
-            int top = 0;  // bucket of the longest tiles
-            while (top < 32 && hist[top] == 0) ++top;
-            const uint64_t longest = top < 32 ? (uint64_t)1 << (31 - top) : 0;  // their lower bound
-            int h0 = rel == 0 || longest >= 2 * rel ? 31 - __builtin_clz((uint32_t)to.split) : 32;
-            while (h0 < 31 && ((uint64_t)1 << h0) < rel) ++h0;
-            for (int h = h0; h <= 31; ++h) {
-                uint32_t c = 0;
-                for (int k = 0; k <= 31 - h; ++k) c += hist[k];
-                if (c <= (uint32_t)kSplitTiles) {
-                    nh = c;
-                    thr = 1u << h;
-                    break;
-                }
-            }
-        }
-        to.order[T] = nh;
-        to.order[T + 1] = thr;
+    if (threadIdx.x < kOrderBuckets) {
+        uint32_t s = 0;
+        for (int i = 0; i < 32; ++i) s += L.copies[threadIdx.x][(i + threadIdx.x) & 31];
+        L.all[threadIdx.x] = s;
     }
     __syncthreads();
 }
 
+// Placement of tiles [chunk NT, chunk NT + NT) by a workgroup of NT threads
+// (with counts, L.all holds the histogram). Ends with a barrier.
+template <int NT>
+__device__ __forceinline__ void tile_place_chunk(const TileOrder& to, int64_t chunk, PlaceLds& L) {
+    uint32_t* cursor = to.hist + kOrderBuckets;
+    const int64_t T = to.T;
+    if (threadIdx.x < kOrderBuckets) L.h[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t t = chunk * NT + threadIdx.x;
+    const bool act = t < T;
+    const int b = act ? order_bucket(to.counts ? to.counts[t] : tile_count(to.offsets, to.sm, t)) : 0;
+    const uint32_t slot = wave_aggregated_add(L.h, b, act);
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+        // lane b: bucket b, its tiles v and all tiles up to it incl
+        const int k = lane();
+        const uint32_t v = k < kOrderBuckets ? (to.counts ? L.all[k] : to.hist[k]) : 0u;
+        const uint32_t incl = wave_inclusive_sum(v);
+        if (k < kOrderBuckets) L.base[k] = L.h[k] ? incl - v + atomicAdd(&cursor[k], L.h[k]) : 0u;
+        if (chunk == 0) {
+            // counts >= 2^h have a bit length > h: buckets 0 .. 31 - h. The
+            // threshold is the smallest power of two >= split and >= `factor`
+            // times the mean count of the non-empty tiles that leaves at most
+            // kSplitTiles tiles above it, so the split set is a union of whole
+            // buckets (independent of the order inside a bucket). Only tiles
+            // far longer than the typical walk are on the critical path, and
+            // only when the longest reach at least twice that bound (a long
+            // tail): where every tile is long the quad walk's extra
+            // instructions per entry cost more than its shorter walks gain.
+            uint32_t nh = 0, thr = 0;
+            if (to.split > 0) {
+                const uint64_t m = to.offsets[to.sm.first(T)];
+                const uint64_t nonempty = (uint64_t)T - shfl_u32(v, 32);
+                // with fewer block wavefronts than the CUs hold (256 x 32), the
+                // quad walks run on otherwise idle SIMDs: no bound from the mean
+                const bool filled = 4 * nonempty >= (uint64_t)kFillWaves;
+                const uint64_t rel = nonempty && filled ? (uint64_t)to.factor * m / nonempty : 0;
+                const uint64_t used = ballot(v != 0) & 0xFFFFFFFFull;
+                const int top = used ? __builtin_ctzll(used) : 32;  // bucket of the longest tiles
+                const uint64_t longest = top < 32 ? (uint64_t)1 << (31 - top) : 0;  // their lower bound
+                int h0 = rel == 0 || longest >= 2 * rel ? 31 - __builtin_clz((uint32_t)to.split) : 32;
+                while (h0 < 31 && ((uint64_t)1 << h0) < rel) ++h0;
+                // the last bucket up to 31 - h0 whose tiles fit
+                const uint64_t fit = ballot(k <= 31 - h0 && incl <= (uint32_t)kSplitTiles);
+                if (fit) {
+                    const int last = 63 - __builtin_clzll(fit);
+                    nh = shfl_u32(incl, last);
+                    thr = 1u << (31 - last);
+                }
+            }
+            if (k == 0) {
+                to.order[T] = nh;
+                to.order[T + 1] = thr;
+            }
+        }
+    }
+    __syncthreads();
+    if (act) to.order[L.base[b] + slot] = (uint32_t)t;
+    __syncthreads();
+}
+
 __global__ void __launch_bounds__(256) tile_place_kernel(TileOrder to) {
-    __shared__ uint32_t h[kOrderBuckets], base[kOrderBuckets];
-    tile_place_chunk<256>(to, blockIdx.x, h, base);
+    __shared__ PlaceLds L;
+    if (to.counts) tile_hist_all<256>(to, L);
+    tile_place_chunk<256>(to, blockIdx.x, L);
 }
 
 // ---------------------------------------------------------------------------
@@ -980,21 +1145,26 @@ hipError_t launch_bin_scatter(const uint32_t* info, int64_t n, const uint32_t* e
     return hipGetLastError();
 }
 
-hipError_t launch_repair(const uint32_t* bin_off, int64_t nseg, uint64_t* pairs, const uint32_t* seg_lists,
-                         const uint32_t* bucket_count, RecordSink rs, bool desc, const TileOrder& to, hipStream_t s) {
+hipError_t launch_repair(const uint32_t* bin_off, int64_t nseg, uint64_t* pairs, uint32_t* seg_lists,
+                         uint32_t* bucket_count, RecordSink rs, bool desc, const TileOrder& to,
+                         const RepairSum& sum, const GroupSplit& sp, const uint16_t* part_tile, hipStream_t s) {
     if (nseg == 0) return launch_tile_place(to, s);
     const unsigned small_blocks = (unsigned)std::min<int64_t>(std::max<int64_t>((nseg + 31) / 32, 1), 4096);
-    if (desc) {
-        hipLaunchKernelGGL(sort_small_kernel<true>, dim3(small_blocks), dim3(256), 0, s, bin_off, seg_lists, nseg,
-                           bucket_count, pairs, rs);
-        hipLaunchKernelGGL(sort_large_kernel<true>, dim3(512), dim3(kLargeThreads), 0, s, bin_off, seg_lists, nseg,
-                           bucket_count, pairs, rs, to);
-    } else {
-        hipLaunchKernelGGL(sort_small_kernel<false>, dim3(small_blocks), dim3(256), 0, s, bin_off, seg_lists, nseg,
-                           bucket_count, pairs, rs);
-        hipLaunchKernelGGL(sort_large_kernel<false>, dim3(512), dim3(kLargeThreads), 0, s, bin_off, seg_lists, nseg,
-                           bucket_count, pairs, rs, to);
-    }
+    if (desc && sp.list)
+        hipLaunchKernelGGL((sort_small_kernel<true, true>), dim3(kPartGrid), dim3(kPartThreads), 0, s, bin_off, seg_lists,
+                           nseg, bucket_count, pairs, rs, sp, part_tile);
+    else if (desc)
+        hipLaunchKernelGGL((sort_small_kernel<true, false>), dim3(small_blocks), dim3(256), 0, s, bin_off, seg_lists,
+                           nseg, bucket_count, pairs, rs, sp, part_tile);
+    else
+        hipLaunchKernelGGL((sort_small_kernel<false, false>), dim3(small_blocks), dim3(256), 0, s, bin_off, seg_lists,
+                           nseg, bucket_count, pairs, rs, sp, part_tile);
+    if (desc)
+        hipLaunchKernelGGL(sort_large_kernel<true>, dim3(kLargeGrid), dim3(kLargeThreads), 0, s, bin_off, seg_lists, nseg,
+                           bucket_count, pairs, rs, to, sum);
+    else
+        hipLaunchKernelGGL(sort_large_kernel<false>, dim3(kLargeGrid), dim3(kLargeThreads), 0, s, bin_off, seg_lists,
+                           nseg, bucket_count, pairs, rs, to, sum);
     return hipGetLastError();
 }
 
@@ -1003,7 +1173,7 @@ hipError_t launch_tile_order(const uint32_t* offsets, SegMap sm, int64_t T, uint
     if (T == 0) return hipSuccess;
     hipLaunchKernelGGL(tile_hist_kernel, dim3(grid_for(T, 256)), dim3(256), 0, s, offsets, sm, T, hist);
     hipLaunchKernelGGL(tile_place_kernel, dim3(grid_for(T, 256)), dim3(256), 0, s,
-                       TileOrder{offsets, sm, T, hist, order, split, factor});
+                       TileOrder{offsets, sm, T, hist, order, split, factor, nullptr});
     return hipGetLastError();
 }
 
@@ -1054,17 +1224,17 @@ hipError_t launch_group_count(const uint32_t* info, int64_t n, const uint32_t* e
 hipError_t launch_group_scatter(const uint32_t* info, int64_t n, const uint32_t* emit_off, const float* zrange,
                                 NearKey nk, GroupMap gm, int tiles_x, int tiles_y, const uint32_t* group_off,
                                 const uint32_t* wgbase, uint64_t* tmp_pair, uint16_t* tmp_code, int64_t capacity,
-                                hipStream_t s) {
+                                const GroupSplit& sp, hipStream_t s) {
     if (n == 0) return hipSuccess;
     const int64_t blocks = (n + kGroupChunk - 1) / kGroupChunk;
     if (gm.seg_base)
         hipLaunchKernelGGL(group_scatter_kernel<true>, dim3((unsigned)blocks), dim3(kScatterThreads), 0, s,
                            reinterpret_cast<const uint4*>(info), n, emit_off, zrange, nk, gm, tiles_x, tiles_y,
-                           group_off, wgbase, tmp_pair, tmp_code, capacity);
+                           group_off, wgbase, tmp_pair, tmp_code, capacity, sp);
     else
         hipLaunchKernelGGL(group_scatter_kernel<false>, dim3((unsigned)blocks), dim3(kScatterThreads), 0, s,
                            reinterpret_cast<const uint4*>(info), n, emit_off, zrange, nk, gm, tiles_x, tiles_y,
-                           group_off, wgbase, tmp_pair, tmp_code, capacity);
+                           group_off, wgbase, tmp_pair, tmp_code, capacity, sp);
     return hipGetLastError();
 }
 

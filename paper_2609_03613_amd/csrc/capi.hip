@@ -112,9 +112,11 @@ struct Layout {
     size_t emit_off, vis_ids, zero, zero_words, status_emit_x, status_emit_y, status_bins, status_segs, status_sel,
         count,
         count_var, tile_seg, entry_rank, seg_lists, keys_in, vals_in, sort_tmp, sort_tmp_bytes, gcount, group_off,
-        wgbase, tmp_pair, tmp_code, group_order, samples, ginfo, total;
+        wgbase, tmp_pair, tmp_code, group_order, samples, ginfo, slices, units, split_hist, part_tile, queued,
+        tile_count, total;
     int64_t list_stride;  // entries per repair bucket list
     GroupMap gm;  // gm.G > 0: grouped binning
+    GroupSplit sp;  // sizes of the split groups' lists (max_slices == 0: none)
 };
 
 // Control words at the start of the zeroed region (uint32 offsets).
@@ -123,6 +125,7 @@ constexpr int kTicketBins = 1;
 constexpr int kTicketSegs = 2;
 constexpr int kTicketSel = 3;
 constexpr int kSelCtl = 4;  // 2 words: first rejected segment + 1, remaining budget
+constexpr int kSplitCtl = 8;  // 3 words: split groups, slices, parts
 constexpr int kBucketCount = 16;
 constexpr int kTileHist = 32;  // 66 words: histogram and cursors of the tile order
 constexpr int kControlWords = 128;
@@ -138,9 +141,10 @@ int end_bit_for(int64_t T) {
 // scan), then the group totals (grouped binning) or the per-XCD counts
 // (uniform K, group shape out of range)] followed by, for BINNED, [depth
 // samples] and then, grouped: [repair lists (uint2 {begin, length} entries
-// with sub-bins)][group offsets][group order][workgroup slice bases]
-// [grouped pairs][grouped codes] and, with per-tile bin counts, [tile
-// segments][group info]; otherwise [entry ranks][repair lists] and, with
+// with sub-bins)][group offsets][group order][queued entries][tile counts]
+// [workgroup slice bases][grouped pairs][grouped codes], with per-tile bin
+// counts [tile segments][group info], and where groups can be split [slices]
+// [parts][split counters][entry tiles]; otherwise [entry ranks][repair lists] and, with
 // per-tile bin counts, [per-XCD counts][tile segments]. GLOBAL: [unsorted
 // keys][unsorted ids][sort scratch]. The zeroed region is cleared by one
 // fill at the start of each tgs_bin; with per-tile bin counts only the
@@ -207,12 +211,31 @@ Layout layout(int64_t n, int64_t capacity, int64_t T, int K, int order, bool var
         L.seg_lists = take(entry * (size_t)kBuckets * (size_t)L.list_stride);
         L.group_off = take(sizeof(uint32_t) * ((size_t)L.gm.G + 1));
         L.group_order = take(sizeof(uint32_t) * (size_t)L.gm.G);
+        L.queued = take(sizeof(uint32_t) * (size_t)L.gm.G);
+        L.tile_count = take(sizeof(uint32_t) * (size_t)T);
         L.wgbase = take(sizeof(uint32_t) * (chunks > 0 ? chunks : 1) * (size_t)L.gm.G);
         L.tmp_pair = take(sizeof(uint64_t) * (size_t)capacity);
         L.tmp_code = take(sizeof(uint16_t) * (size_t)capacity);
         if (var) {
             L.tile_seg = take(sizeof(uint2) * (size_t)T);
             L.ginfo = take(sizeof(uint4) * (size_t)L.gm.G);
+        }
+        // groups are split with sub-bins (exact repair without records), when
+        // the capacity allows groups that long
+        if (L.gm.SB > 1 && capacity > (int64_t)kSplitMin && capacity > L.gm.G * kSplitMean) {
+            GroupSplit& sp = L.sp;
+            sp.max_groups = (int)std::min<int64_t>(L.gm.G, capacity / (kSplitMin + 1) + 1);
+            sp.max_slices = (int)(capacity / kSlice) + sp.max_groups;
+            sp.max_units = (int)(3 * capacity / kPartLen) + sp.max_groups;
+            // the slices are counted beside the groups that are not split; with
+            // 512 workgroups for them, where there are few, a 1297x840 training
+            // step took 770 us instead of 753
+            sp.slice_grid = std::min(sp.max_slices, 128);
+            sp.stride = std::min(L.gm.GS * L.gm.SB, kMaxGroupSegs) + kMaxParts;
+            L.slices = take(sizeof(uint4) * (size_t)sp.max_slices);
+            L.units = take(sizeof(uint4) * (size_t)sp.max_units);
+            L.split_hist = take(sizeof(uint32_t) * (size_t)sp.max_groups * (size_t)sp.stride);
+            L.part_tile = take(sizeof(uint16_t) * (size_t)capacity);
         }
     } else if (order == TGS_ORDER_BINNED) {
         L.entry_rank = take(sizeof(uint32_t) * (size_t)capacity);
@@ -554,18 +577,30 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
                            out->zrange_dev, (uint32_t*)(w + L.samples)};
         TGS_HIP(launch_group_count(pr->info_dev, n, emit_off, gm, tiles_x, tiles_y, gcount, wgbase, ra, s),
                 "depth range and group count");
-        TGS_HIP(launch_group_scan(gcount, gm, group_off, group_order, s), "group scan");
+        GroupSplit sp = L.sp;
+        if (sp.max_slices > 0) {
+            sp.list = (uint4*)(w + L.slices);
+            sp.units = (uint4*)(w + L.units);
+            sp.hist = (uint32_t*)(w + L.split_hist);
+            sp.ctl = zero + kSplitCtl;
+        }
+        TGS_HIP(launch_group_scan(gcount, gm, group_off, group_order, cap, sp, s), "group scan");
         TGS_HIP(launch_group_scatter(pr->info_dev, n, emit_off, out->zrange_dev, nk, gm, tiles_x, tiles_y, group_off,
-                                     wgbase, tmp_pair, tmp_code, cap, s),
+                                     wgbase, tmp_pair, tmp_code, cap, sp, s),
                 "group scatter");
-        // the group sort adds the tile-order histogram; the placement rides on
-        // the repair's long-segment launch
-        const TileOrder to{out->offsets_dev, sm, T, zero + kTileHist, out->tile_order_dev, params->split_entries,
-                           params->split_mean_factor};
+        // the group sort leaves the entries per tile; the tile order's placement
+        // rides on the repair's long-segment launch. Past kCountedTiles the
+        // histogram each workgroup would make for itself costs more than the
+        // tile order's own two launches.
+        uint32_t* tile_count = out->tile_order_dev && T <= kCountedTiles ? (uint32_t*)(w + L.tile_count) : nullptr;
+        const TileOrder to{out->offsets_dev, sm, T, zero + kTileHist, tile_count ? out->tile_order_dev : nullptr,
+                           params->split_entries, params->split_mean_factor, tile_count};
+        uint32_t* queued = (uint32_t*)(w + L.queued);
+        const bool all = params->repair == TGS_REPAIR_ALL;
+        const RepairSum sum{all ? queued : nullptr, gm.G, out->counters_dev};
         TGS_HIP(launch_group_sort(tmp_pair, tmp_code, group_off, group_order, gm, nseg, cap, out->pairs_dev,
-                                  out->offsets_dev, seg_lists, L.list_stride, bucket_count, out->counters_dev,
-                                  params->repair == TGS_REPAIR_ALL, out->repaired_dev, rs,
-                                  to.order ? to.hist : nullptr, s),
+                                  out->offsets_dev, seg_lists, L.list_stride, bucket_count, out->counters_dev, all,
+                                  out->repaired_dev, rs, queued, tile_count, sp, (uint16_t*)(w + L.part_tile), s),
                 "group sort");
         if (rules)
             TGS_HIP(launch_repair_select(out->offsets_dev, T, K, params->repair_budget, zero + kTicketSel,
@@ -575,10 +610,14 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
         // with sub-bins the queues hold sub-segment descriptors
         if (params->repair != TGS_REPAIR_NONE)
             TGS_HIP(launch_repair(out->offsets_dev, L.list_stride, out->pairs_dev, seg_lists, bucket_count, rs,
-                                  gm.SB > 1, to, s),
+                                  gm.SB > 1, to, sum, sp, (const uint16_t*)(w + L.part_tile), s),
                     "repair and tile order");
         else
             TGS_HIP(launch_tile_place(to, s), "tile order");
+        if (out->tile_order_dev && !tile_count)
+            TGS_HIP(launch_tile_order(out->offsets_dev, sm, T, zero + kTileHist, out->tile_order_dev,
+                                      params->split_entries, params->split_mean_factor, s),
+                    "tile order");
         return read_count();
     }
     TGS_HIP(launch_depth_range(pr->info_dev, vis_ids, out->counters_dev, nk, S, params->p_lo, params->p_hi,
@@ -601,7 +640,7 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
             "bin scatter");
     if (params->repair != TGS_REPAIR_NONE)
         TGS_HIP(launch_repair(out->offsets_dev, nseg, out->pairs_dev, seg_lists, bucket_count, rs, false, TileOrder{},
-                              s),
+                              RepairSum{}, GroupSplit{}, nullptr, s),
                 "repair");
     if (out->tile_order_dev)
         TGS_HIP(launch_tile_order(out->offsets_dev, sm, T, zero + kTileHist, out->tile_order_dev,

@@ -238,6 +238,39 @@ GroupMap group_map(int64_t T, int K, int sub);
 // min(8, kMaxGroupSegs / K) tiles; sub-bins are chosen per group.
 GroupMap group_map_var(int64_t T, int K, int sub);
 
+// Long groups (exact repair with sub-bins): a group of more than kSplitMin
+// entries is split over the chip, by slices of kSlice entries that are ordered
+// by part first; a part is a run of codes with at most 2 kPartLen entries, or
+// one code. One workgroup per group took as long as its longest group: 112 us
+// of group sort on 640x360 with one million Gaussians (now 40 and 45 for the
+// parts), 398 us on 1920x1080 with 10 million (now 60 and 350), with 250 us in
+// the sort of the longest sub-segment behind it (now 37). The line at 16384
+// entries: a split group is read and written once more, which pays where the
+// group sort's scattered stores and the queued sub-segments cost more than that
+// (binning of 10 million Gaussians 1048 us, 1060 at 8192 and 1072 at 32768; a
+// 1297x840 training step 743, 765 and 755). kSplitMean: below 4096 entries of
+// capacity per group, groups that long are rare, and the extra launch and the
+// larger one that mostly find nothing cost 10 us (the frame of one million on
+// 1920x1080, 3922 per group: 397 us against 389).
+constexpr int kSlice = 4096;       // entries per slice workgroup
+constexpr int kPartLen = 2048;     // entries between part boundaries
+constexpr int kMaxParts = 2048;    // LDS counters of one slice workgroup
+constexpr uint32_t kSplitMin = 16384;
+constexpr int64_t kSplitMean = 4096;
+// n / kPartLen stretches and two boundaries per code of more than kPartLen
+// entries: at most 3 n / kPartLen + 1 parts. Longer groups are sorted whole.
+constexpr uint32_t kSplitMax = (uint32_t)(kMaxParts - 1) / 3 * kPartLen;
+__host__ __device__ __forceinline__ bool split_group(uint32_t n) { return n > kSplitMin && n <= kSplitMax; }
+struct GroupSplit {
+    uint4* list;      // slices {group, split index, begin, end}; null: no split groups
+    uint4* units;     // parts of the split groups {begin, length, first tile of the group, tiles}
+    uint32_t* hist;   // [split groups][stride]: entries per code, then the part cursors [kMaxParts]
+    uint32_t* ctl;    // split groups, slices, parts (zero before)
+    int stride;
+    int max_groups, max_slices, max_units;  // split groups and list lengths
+    int slice_grid;  // workgroups for the slices in the group sort's launch
+};
+
 // Per-tile bin counts: seg_base [T + 1] is the exclusive prefix sum of the
 // counts (powers of two), first(t) = seg_base[t], and the number of
 // segments S = seg_base[T] is known on the device only.
@@ -392,27 +425,31 @@ hipError_t launch_bin_scatter(const uint32_t* info, int64_t n, const uint32_t* e
 // [S + 1] (S = T K), repair queues and repaired[] as launch_bin_offsets,
 // single-entry segments' records; bucket_count must be zero. With SB > 1
 // the repair queues hold sub-segments as uint2 {begin, length} (list stride
-// list_stride entries); repaired[] and counters[3] stay per segment.
-// tile_hist != null: also adds each tile's bit-length bucket to the tile
-// order histogram tile_hist [33] (zero before), so that only the placement
-// half of the tile order is left (TileOrder). With SB > 1, a group of at
+// list_stride entries); repaired[] stays per segment. queued [G]: the entries
+// of each group's repaired segments (their sum, counters[3], is left to the
+// repair, see RepairSum). tile_count [T] (optional): each tile's entries, for
+// the tile order. With SB > 1, a group of at
 // most 4096 entries is staged through LDS and its sub-segments of up to 128
-// entries come out in pair order (they are not queued).
+// entries come out in pair order (they are not queued). With sp.list, longer
+// groups are split (the group scan lists their slices, the group scatter
+// clears their counters) and come out in pair order too, except the queued
+// sub-segments; part_tile [capacity] is scratch for their entries' tiles.
 // The group count needs no bins; its first workgroup computes the depth
 // range (ra) meanwhile, which the group scatter then uses.
 hipError_t launch_group_count(const uint32_t* info, int64_t n, const uint32_t* emit_off, GroupMap gm, int tiles_x,
                               int tiles_y, uint32_t* gcount, uint32_t* wgbase, const RangeArgs& ra, hipStream_t s);
 hipError_t launch_group_scan(const uint32_t* gcount, GroupMap gm, uint32_t* group_off, uint32_t* order,
-                             hipStream_t s);
+                             int64_t capacity, const GroupSplit& sp, hipStream_t s);
 hipError_t launch_group_scatter(const uint32_t* info, int64_t n, const uint32_t* emit_off, const float* zrange,
                                 NearKey nk, GroupMap gm, int tiles_x, int tiles_y, const uint32_t* group_off,
                                 const uint32_t* wgbase, uint64_t* tmp_pair, uint16_t* tmp_code, int64_t capacity,
-                                hipStream_t s);
+                                const GroupSplit& sp, hipStream_t s);
 hipError_t launch_group_sort(const uint64_t* tmp_pair, const uint16_t* tmp_code, const uint32_t* group_off,
                              const uint32_t* order, GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* pairs, uint32_t* bin_off,
                              uint32_t* lists, int64_t list_stride, uint32_t* bucket_count,
-                             int64_t* counters, bool queue_all, uint8_t* repaired, RecordSink rs,
-                             uint32_t* tile_hist, hipStream_t s);
+                             const int64_t* counters, bool queue_all, uint8_t* repaired, RecordSink rs,
+                             uint32_t* queued, uint32_t* tile_count, const GroupSplit& sp, uint16_t* part_tile,
+                             hipStream_t s);
 
 // Per-tile bin counts: seg_base[t] = exclusive prefix sum of the bin counts
 // (each clamped to 1..kmax and rounded down to a power of two), seg_base[T]
@@ -425,9 +462,11 @@ hipError_t launch_seg_base(const int32_t* per_tile_bins, int64_t T, int kmax, ui
 hipError_t launch_fill_u32_dyn(uint32_t* p, uint32_t v, const uint32_t* n_dev, int mult, int64_t max_n,
                                hipStream_t s);
 
-// Placement half of the tile order (launch_tile_order below) over a
-// histogram that is already complete: hist [33] per bit-length bucket, then
-// the 33 placement cursors, zero. order == null: none.
+// Placement half of the tile order (launch_tile_order below). counts ==
+// null: over a histogram that is already complete, hist [33] per bit-length
+// bucket, then the 33 placement cursors, zero. Otherwise from the entries
+// per tile counts [T] (at most kCountedTiles): every workgroup makes the
+// histogram for itself, and only the cursors are shared. order == null: none.
 struct TileOrder {
     const uint32_t* offsets;
     SegMap sm;
@@ -435,15 +474,24 @@ struct TileOrder {
     uint32_t* hist;
     uint32_t* order;
     int split, factor;
+    const uint32_t* counts;
+};
+constexpr int64_t kCountedTiles = 65536;
+// counters[3] = the sum of queued [G] (null: nothing to sum).
+struct RepairSum {
+    const uint32_t* queued;
+    int G;
+    int64_t* counters;
 };
 
 // Sorts every queued segment by its 64-bit pairs and writes its records.
 // The lists hold segment ids located by bin_off (list stride nseg), or with
 // desc uint2 {begin, length} entries (sub-segments; no records). to.order !=
 // null: the last workgroups of the long-segment launch also place the tiles
-// (the sorts do not change the offsets).
-hipError_t launch_repair(const uint32_t* bin_off, int64_t nseg, uint64_t* pairs, const uint32_t* seg_lists,
-                         const uint32_t* bucket_count, RecordSink rs, bool desc, const TileOrder& to, hipStream_t s);
+// (the sorts do not change the offsets), and sum adds up counters[3] there.
+hipError_t launch_repair(const uint32_t* bin_off, int64_t nseg, uint64_t* pairs, uint32_t* seg_lists,
+                         uint32_t* bucket_count, RecordSink rs, bool desc, const TileOrder& to,
+                         const RepairSum& sum, const GroupSplit& sp, const uint16_t* part_tile, hipStream_t s);
 // The placement half alone (tile order after a grouped sort without repair).
 hipError_t launch_tile_place(const TileOrder& to, hipStream_t s);
 

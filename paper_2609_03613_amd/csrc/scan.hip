@@ -12,6 +12,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "wave_sort.hpp"
 
 namespace tgs {
 
@@ -633,9 +634,13 @@ __global__ void __launch_bounds__(kThreads) seg_base_kernel(const int32_t* __res
 // (one workgroup; G <= kMaxGroups = 8 per thread), and order[0 .. G) = the
 // groups by decreasing floor(log2(count)) (empty groups last; arbitrary
 // inside a class), so that the group sort starts the longest groups first.
+// With sp.list, also the slices of kSlice entries of the groups that are
+// split, sp.list[i] = {group, index among the split groups, begin, end}, and
+// sp.ctl [0] = split groups, [1] = slices.
 __global__ void __launch_bounds__(kTailThreads) group_scan_kernel(const uint32_t* __restrict__ gcount, GroupMap gm,
                                                                   uint32_t* __restrict__ group_off,
-                                                                  uint32_t* __restrict__ order) {
+                                                                  uint32_t* __restrict__ order, int64_t capacity,
+                                                                  GroupSplit sp) {
     const int G = gm.G;
     // per-tile bin counts: each group's first segment, segment count and the
     // most sub-bins (up to SB) whose codes fit the group sort's counters
@@ -653,24 +658,76 @@ __global__ void __launch_bounds__(kTailThreads) group_scan_kernel(const uint32_t
     __shared__ uint32_t lds[kTailThreads / kWave];
     __shared__ uint32_t chist[kClasses], cbase[kClasses];
     if (threadIdx.x < kClasses) chist[threadIdx.x] = 0;
-    const int i0 = 8 * threadIdx.x;
+    // consecutive groups per thread, as few as cover them
+    const int per = (G + kTailThreads - 1) / kTailThreads, i0 = per * threadIdx.x;
     uint32_t v[8], s = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        v[j] = i0 + j < G ? gcount[i0 + j] : 0u;
+        v[j] = j < per && i0 + j < G ? gcount[i0 + j] : 0u;
         s += v[j];
     }
     uint32_t total;
     uint32_t run = tail_excl_u32(s, lds, &total);  // ends with a barrier: chist is cleared
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        if (i0 + j < G) {
+        if (j < per && i0 + j < G) {
             group_off[i0 + j] = run;
             atomicAdd(&chist[v[j] ? __builtin_clz(v[j]) : 32], 1u);
         }
         run += v[j];
     }
     if (threadIdx.x == 0) group_off[G] = total;
+    if (sp.list) {
+        // each split group's first slice, then all threads list the slices
+        // (binary search over the groups)
+        __shared__ uint32_t first_item[kMaxGroups];
+        __shared__ uint16_t group_id[kMaxGroups];
+        run -= s;  // the thread's first group again
+        uint32_t n[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t lo = (uint32_t)min((int64_t)run, capacity);
+            run += v[j];
+            n[j] = (uint32_t)min((int64_t)run, capacity) - lo;
+        }
+        uint32_t ng = 0, ns = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const bool in = split_group(n[j]);
+            ng += in ? 1u : 0u;
+            ns += in ? (n[j] + kSlice - 1) / kSlice : 0u;
+        }
+        uint32_t all_g, all_s;
+        uint32_t h = tail_excl_u32(ng, lds, &all_g), at = tail_excl_u32(ns, lds, &all_s);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (!split_group(n[j])) continue;
+            first_item[h] = at;
+            group_id[h++] = (uint16_t)(i0 + j);
+            at += (n[j] + kSlice - 1) / kSlice;
+        }
+        // (only an entry count that wrapped can exceed the bounds)
+        if (all_s > (uint32_t)sp.max_slices || all_g > (uint32_t)sp.max_groups) all_s = all_g = 0;
+        if (threadIdx.x == 0) {
+            sp.ctl[0] = all_g;
+            sp.ctl[1] = all_s;
+        }
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < all_s; i += kTailThreads) {
+            uint32_t a = 0, b = all_g;  // first_item[a] <= i < first_item[b]
+            while (b - a > 1) {
+                const uint32_t mid = (a + b) / 2;
+                if (first_item[mid] <= i)
+                    a = mid;
+                else
+                    b = mid;
+            }
+            const uint32_t g = group_id[a], k = i - first_item[a];
+            const uint32_t lo = (uint32_t)min((int64_t)group_off[g], capacity);
+            const uint32_t hi = (uint32_t)min((int64_t)group_off[g + 1], capacity);
+            sp.list[i] = make_uint4(g, a, lo + k * kSlice, min(lo + (k + 1) * kSlice, hi));
+        }
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t b = 0;
@@ -682,7 +739,7 @@ __global__ void __launch_bounds__(kTailThreads) group_scan_kernel(const uint32_t
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-        if (i0 + j < G) order[atomicAdd(&cbase[v[j] ? __builtin_clz(v[j]) : 32], 1u)] = (uint32_t)(i0 + j);
+        if (j < per && i0 + j < G) order[atomicAdd(&cbase[v[j] ? __builtin_clz(v[j]) : 32], 1u)] = (uint32_t)(i0 + j);
 }
 
 #ifndef TGS_SORT_THREADS
@@ -691,17 +748,8 @@ __global__ void __launch_bounds__(kTailThreads) group_scan_kernel(const uint32_t
 #ifndef TGS_SORT_BATCH
 #define TGS_SORT_BATCH (8192 / TGS_SORT_THREADS)
 #endif
-#ifndef TGS_SORT_WAVES_PER_EU
-#define TGS_SORT_WAVES_PER_EU 0
-#endif
-#if TGS_SORT_WAVES_PER_EU > 0
-#define TGS_SORT_ATTR __attribute__((amdgpu_waves_per_eu(TGS_SORT_WAVES_PER_EU, TGS_SORT_WAVES_PER_EU)))
-#else
-#define TGS_SORT_ATTR
-#endif
 constexpr int kSortThreads = TGS_SORT_THREADS;  // threads of a group-sort workgroup
 constexpr int kSortBatch = TGS_SORT_BATCH;      // entries per thread and sweep step, loaded before any is used
-constexpr int kTileBuckets = 33;                  // tile order buckets: bit lengths 32 .. 0 of the entry count
 
 // Staging of the group sort's output when the lists hold sub-segment
 // descriptors (SB > 1: exact repair, no records) and the group has at most
@@ -711,14 +759,116 @@ constexpr int kTileBuckets = 33;                  // tile order buckets: bit len
 // written out in order: the output is written in runs instead of one
 // scattered 8-byte store per entry, and the short sub-segments need no
 // repair pass.
-#ifndef TGS_RANK_MAX
-#define TGS_RANK_MAX 128
-#endif
 #ifndef TGS_STAGE
 #define TGS_STAGE 4096
 #endif
 constexpr int kStage = TGS_STAGE;
-constexpr int kRankMax = TGS_RANK_MAX;
+constexpr int kRankMax = 128;
+
+// The segments and codes of group g: segments [sbase, sbase + segs), SB
+// sub-bins each, entry codes 0 .. segs SB - 1; nseg = all segments.
+struct GroupCodes {
+    int64_t sbase, segs, nseg;
+    int SB, codes;
+};
+__device__ __forceinline__ GroupCodes codes_of(const GroupMap& gm, int g, int64_t nseg) {
+    GroupCodes c;
+    if (gm.seg_base) {
+        const uint4 gi = gm.ginfo[g];
+        c.sbase = gi.x;
+        c.segs = gi.y;
+        c.SB = 1 << gi.z;
+        c.nseg = gm.seg_base[gm.T];
+    } else {
+        c.sbase = (int64_t)g * gm.GS;
+        c.segs = min((int64_t)gm.GS, nseg - c.sbase);
+        c.SB = gm.SB;
+        c.nseg = nseg;
+    }
+    c.codes = (int)(c.segs * c.SB);
+    return c;
+}
+// First code of tile t of the group (tiles g GT ..).
+__device__ __forceinline__ int64_t first_code(const GroupMap& gm, const GroupCodes& c, int g, int64_t t) {
+    return gm.seg_base ? ((int64_t)gm.seg_base[t] - c.sbase) * c.SB : (t - (int64_t)g * gm.GT) * gm.K * c.SB;
+}
+
+// Per-group results from pre[] (LDS), the exclusive prefix of the group's n
+// entries over its codes: the bin offsets and repair flags of its segments,
+// the entries of its repaired segments (queued[g]) and of its tiles
+// (tile_count[t], optional). lds32: NT / 64 words. Per-group values go to
+// arrays that a later launch sums: a thousand workgroups adding to one word
+// would wait for each other (25 to 50 ns each).
+template <int NT>
+__device__ __forceinline__ void group_results(const GroupMap& gm, const GroupCodes& gc, int g, uint32_t lo, uint32_t n,
+                                              const uint32_t* pre, bool queue, uint32_t* __restrict__ bin_off,
+                                              uint8_t* __restrict__ repaired, uint32_t* __restrict__ queued_out,
+                                              uint32_t* __restrict__ tile_count, uint32_t* lds32) {
+    if (tile_count) {
+        // entries per tile: difference of the prefixes at the tiles' first
+        // codes, as the bin offsets will give them
+        const int64_t t0 = (int64_t)g * gm.GT, t1 = min(t0 + gm.GT, (int64_t)gm.T);
+        auto before = [&](int64_t t) -> uint32_t {
+            if (t >= t1) return n;
+            const int64_t c = first_code(gm, gc, g, t);
+            return c < gc.codes ? pre[c] : n;
+        };
+        for (int64_t t = t0 + threadIdx.x; t < t1; t += NT) tile_count[t] = before(t + 1) - before(t);
+    }
+    uint32_t queued = 0;
+    for (int c = threadIdx.x; c < gc.segs; c += NT) {
+        const uint32_t b = pre[c * gc.SB], len = (c + 1 < gc.segs ? pre[(c + 1) * gc.SB] : n) - b;
+        bin_off[gc.sbase + c] = lo + b;
+        const bool rep = queue && len >= 2;
+        if (repaired) repaired[gc.sbase + c] = rep ? 1 : 0;
+        if (rep) queued += len;
+    }
+    if (g == gm.G - 1 && threadIdx.x == 0) bin_off[gc.nseg] = lo + n;
+    const uint32_t qsum = block_sum_u32<NT>(queued, lds32);
+    if (threadIdx.x == 0) queued_out[g] = qsum;
+}
+
+// Parts of a long group. Its codes are cut into parts that fit the stage:
+// every kPartLen entries (at the next code), and around any code of more than
+// kPartLen entries, which is a part by itself; so every other part has less
+// than 2 kPartLen = kStage entries.
+static_assert(2 * kPartLen == kStage, "parts fit the stage");
+
+// Thread t holds the counts cnt[] of codes t PER .. and run, the entries
+// before them; prev is the count of the code before. flag[j] = a part starts
+// at the thread's code j; returns the number of starts after code 0.
+template <int PER>
+__device__ __forceinline__ uint32_t part_starts(const uint32_t (&cnt)[PER], uint32_t run, uint32_t prev, int codes,
+                                                uint32_t (&flag)[PER]) {
+    uint32_t flags = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int k = (int)threadIdx.x * PER + j;
+        const uint32_t len = cnt[j];
+        flag[j] = k > 0 && k < codes &&
+                          (run / kPartLen != (run - prev) / kPartLen || len > kPartLen || prev > kPartLen)
+                      ? 1u
+                      : 0u;
+        flags += flag[j];
+        run += len;
+        prev = len;
+    }
+    return flags;
+}
+
+// Tile of group g that code k belongs to, relative to the group's first.
+__device__ __forceinline__ uint32_t tile_of_code(const GroupMap& gm, const GroupCodes& gc, int g, uint32_t k) {
+    if (!gm.seg_base) return k / (uint32_t)(gm.K * gc.SB);
+    uint32_t t = 0, end = (uint32_t)min((int64_t)gm.GT, gm.T - (int64_t)g * gm.GT);
+    while (end - t > 1) {
+        const uint32_t mid = (t + end) / 2;
+        if (first_code(gm, gc, g, (int64_t)g * gm.GT + mid) <= (int64_t)k)
+            t = mid;
+        else
+            end = mid;
+    }
+    return t;
+}
 
 // One workgroup per group: its entries [group_off[g], group_off[g + 1])
 // (clipped to the capacity) are counted per code (segment, or sub-segment
@@ -728,57 +878,91 @@ constexpr int kRankMax = TGS_RANK_MAX;
 // queues the repair segments (as bin_offsets_kernel; sub-segments as
 // {begin, length} when SB > 1, without those the staging ordered), and
 // writes the records of single-entry segments.
-__global__ void __launch_bounds__(kSortThreads) TGS_SORT_ATTR group_sort_kernel(
+// With sp.list, the groups that are split are left out here, and the first
+// sp.slice_grid workgroups count their entries per code, slice by slice, into
+// sp.hist (see group_split_kernel).
+__global__ void __launch_bounds__(kSortThreads, 4) group_sort_kernel(
     const uint64_t* __restrict__ tmp_pair, const uint16_t* __restrict__ tmp_code, const uint32_t* __restrict__ group_off,
     const uint32_t* __restrict__ order, GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* __restrict__ pairs,
     uint32_t* __restrict__ bin_off, uint32_t* __restrict__ lists, int64_t list_stride,
-    uint32_t* __restrict__ bucket_count, int64_t* __restrict__ counters, bool queue_all, uint8_t* __restrict__ repaired,
-    RecordSink rs, uint32_t* __restrict__ tile_hist) {
+    uint32_t* __restrict__ bucket_count, const int64_t* __restrict__ counters, bool queue_all,
+    uint8_t* __restrict__ repaired, RecordSink rs, uint32_t* __restrict__ queued, uint32_t* __restrict__ tile_count,
+    GroupSplit sp) {
     constexpr int NT = kSortThreads;
     constexpr int kMaxPer = kMaxGroupSegs / NT;
     constexpr uint32_t kNone = 0xFFFFFFFFu;
     __shared__ uint32_t hist[kMaxGroupSegs];
     __shared__ uint32_t cur[kMaxGroupSegs];
+    __shared__ uint64_t stage[kStage + kRankPad];
+    __shared__ uint16_t scode[kStage];
     __shared__ uint32_t lds32[NT / kWave];
     __shared__ uint32_t lcount[kBuckets], lbase[kBuckets];
-    __shared__ uint32_t thist[kTileBuckets];
-    __shared__ uint64_t stage[kStage];
-    __shared__ uint16_t scode[kStage];
-    const int g = (int)order[blockIdx.x];
+    // adds the codes of entries [lo, hi) to hist
+    auto count = [&](uint32_t lo, uint32_t hi) {
+        for (uint32_t base = lo; base < hi; base += NT * kSortBatch) {
+            uint32_t c[kSortBatch];
+#pragma unroll
+            for (int j = 0; j < kSortBatch; ++j) {
+                const uint32_t e = base + (uint32_t)(j * NT) + threadIdx.x;
+                c[j] = e < hi ? (uint32_t)tmp_code[e] : kNone;
+            }
+#pragma unroll
+            for (int j = 0; j < kSortBatch; ++j)
+                if (c[j] != kNone) atomicAdd(&hist[c[j]], 1u);
+        }
+    };
+    if ((int)blockIdx.x < sp.slice_grid) {
+        // a run of consecutive slices; those of one group are contiguous and
+        // are added to its hist together
+        const uint32_t slices = sp.ctl[1], per = (slices + sp.slice_grid - 1) / sp.slice_grid;
+        const uint32_t end = min((blockIdx.x + 1) * per, slices);
+        for (uint32_t i = blockIdx.x * per; i < end;) {
+            const uint4 first = sp.list[i];
+            uint32_t stop = first.w;
+            for (++i; i < end; ++i) {
+                const uint4 next = sp.list[i];
+                if (next.y != first.y) break;
+                stop = next.w;
+            }
+            const int codes = codes_of(gm, (int)first.x, nseg).codes;
+            for (int c = threadIdx.x; c < codes; c += NT) hist[c] = 0;
+            __syncthreads();
+            count(first.z, stop);
+            __syncthreads();
+            uint32_t* gh = sp.hist + (int64_t)first.y * sp.stride;
+            for (int c = threadIdx.x; c < codes; c += NT)
+                if (hist[c]) atomicAdd(&gh[c], hist[c]);
+        }
+        return;
+    }
+    const int g = (int)order[blockIdx.x - sp.slice_grid];
     const int64_t cap = capacity;
     const uint32_t lo = (uint32_t)min((int64_t)group_off[g], cap);
     const uint32_t hi = (uint32_t)min((int64_t)group_off[g + 1], cap);
-    // the group's segments [sbase, sbase + segs), sub-bins SB, codes segs SB
-    int64_t sbase, segs;
-    int SB;
-    if (gm.seg_base) {
-        const uint4 gi = gm.ginfo[g];
-        sbase = gi.x;
-        segs = gi.y;
-        SB = 1 << gi.z;
-        nseg = gm.seg_base[gm.T];
-    } else {
-        sbase = (int64_t)g * gm.GS;
-        segs = min((int64_t)gm.GS, nseg - sbase);
-        SB = gm.SB;
+    if (sp.list && split_group(hi - lo)) return;
+    const GroupCodes gc = codes_of(gm, g, nseg);
+    if (lo == hi) {  // an empty group: offsets only
+        for (int c = threadIdx.x; c < gc.segs; c += NT) {
+            bin_off[gc.sbase + c] = lo;
+            if (repaired) repaired[gc.sbase + c] = 0;
+        }
+        const int64_t t0 = (int64_t)g * gm.GT;
+        if (tile_count)
+            for (int64_t t = t0 + threadIdx.x; t < min(t0 + gm.GT, (int64_t)gm.T); t += NT) tile_count[t] = 0;
+        if (threadIdx.x == 0) {
+            queued[g] = 0;
+            if (g == gm.G - 1) bin_off[gc.nseg] = lo;
+        }
+        return;
     }
-    const int codes = (int)(segs * SB);
+    const int codes = gc.codes;
     const int per = (codes + NT - 1) / NT;  // codes per thread, <= kMaxPer
     for (int c = threadIdx.x; c < per * NT; c += NT) hist[c] = 0;
     if (threadIdx.x < kBuckets) lcount[threadIdx.x] = 0;
-    if (threadIdx.x < kTileBuckets) thist[threadIdx.x] = 0;
     __syncthreads();
-    for (uint32_t base = lo; base < hi; base += NT * kSortBatch) {
-        uint32_t c[kSortBatch];
-#pragma unroll
-        for (int j = 0; j < kSortBatch; ++j) {
-            const uint32_t e = base + (uint32_t)(j * NT) + threadIdx.x;
-            c[j] = e < hi ? (uint32_t)tmp_code[e] : kNone;
-        }
-#pragma unroll
-        for (int j = 0; j < kSortBatch; ++j)
-            if (c[j] != kNone) atomicAdd(&hist[c[j]], 1u);
-    }
+    const uint32_t n = hi - lo;
+    const bool staged = gm.SB > 1 && n <= (uint32_t)kStage;
+    count(lo, hi);
     __syncthreads();
     // exclusive prefix of the code counts: thread i owns codes i per ..
     uint32_t ex[kMaxPer], sum = 0;
@@ -793,25 +977,7 @@ __global__ void __launch_bounds__(kSortThreads) TGS_SORT_ATTR group_sort_kernel(
     for (int j = 0; j < kMaxPer; ++j)
         if (j < per) cur[threadIdx.x * per + j] = tex + ex[j];
     __syncthreads();
-    if (tile_hist) {
-        // entries per tile of the group (tiles g GT ..): difference of the
-        // exclusive prefixes at the tiles' first codes, as the bin offsets
-        // will give them; bucket = bit length of the count
-        const int64_t t0 = (int64_t)g * gm.GT, t1 = min(t0 + gm.GT, (int64_t)gm.T);
-        auto first_code = [&](int64_t t) -> uint32_t {
-            if (t >= t1) return hi - lo;
-            const int64_t c = gm.seg_base ? ((int64_t)gm.seg_base[t] - sbase) * SB : (t - t0) * gm.K * SB;
-            return c < codes ? cur[c] : hi - lo;
-        };
-        for (int64_t t = t0 + threadIdx.x; t < t1; t += NT) {
-            const uint32_t cnt = first_code(t + 1) - first_code(t);
-            atomicAdd(&thist[cnt ? __builtin_clz(cnt) : 32], 1u);
-        }
-    }
     const bool queue = queue_all && counters[2] == 0;
-    const int64_t cbase = sbase * gm.SB;  // id of the group's first code
-    const uint32_t n = hi - lo;
-    const bool staged = gm.SB > 1 && n <= (uint32_t)kStage;
     // sub-segments the staging puts in order (none with an overflow)
     const uint32_t local_max = staged && queue ? (uint32_t)kRankMax : 1u;
     // repair queues per code (segments when SB == 1, sub-segments otherwise)
@@ -824,18 +990,6 @@ __global__ void __launch_bounds__(kSortThreads) TGS_SORT_ATTR group_sort_kernel(
             if (queue && hist[c] > local_max) bk[r] = bucket_of(hist[c]);
         }
     }
-    // offsets, repair flags and repaired entries per segment
-    uint32_t queued = 0;
-    for (int c = threadIdx.x; c < segs; c += NT) {
-        const int64_t sg = sbase + c;
-        uint32_t len = 0;
-        for (int k = 0; k < SB; ++k) len += hist[c * SB + k];
-        bin_off[sg] = lo + cur[c * SB];
-        const bool rep = queue && len >= 2;
-        if (repaired) repaired[sg] = rep ? 1 : 0;
-        if (rep) queued += len;
-    }
-    if (g == gm.G - 1 && threadIdx.x == 0) bin_off[nseg] = hi;
     if (gm.SB > 1)
         // sub-segments are queued as {begin, length}: the repair needs no offset lookup
         queue_values<kMaxPer, NT>(
@@ -846,12 +1000,9 @@ __global__ void __launch_bounds__(kSortThreads) TGS_SORT_ATTR group_sort_kernel(
             },
             list_stride, lcount, lbase, reinterpret_cast<uint2*>(lists), bucket_count);
     else
-        queue_segments<kMaxPer, NT>(bk, cbase, list_stride, lcount, lbase, lists, bucket_count);
-    if (queue) {
-        const uint32_t qsum = block_sum_u32<NT>(queued, lds32);
-        if (threadIdx.x == 0 && qsum)
-            atomicAdd(reinterpret_cast<unsigned long long*>(&counters[3]), (unsigned long long)qsum);
-    }
+        queue_segments<kMaxPer, NT>(bk, gc.sbase, list_stride, lcount, lbase, lists, bucket_count);
+    // ends with a barrier: the offsets are read (here and above) before the placement moves them
+    group_results<NT>(gm, gc, g, lo, n, cur, queue, bin_off, repaired, queued, tile_count, lds32);
     if (staged) {
         // place at the code offsets in LDS ...
         for (uint32_t base = lo; base < hi; base += NT * kSortBatch) {
@@ -882,16 +1033,8 @@ __global__ void __launch_bounds__(kSortThreads) TGS_SORT_ATTR group_sort_kernel(
             const uint64_t v = stage[q];
             uint32_t out = q;
             const uint32_t len = hist[c];
-            if (len >= 2 && len <= local_max) {
-                // the code's slots are [cur - len, cur) once placed
-                const uint32_t b = cur[c] - len;
-                uint32_t rank = 0;
-                for (uint32_t k = 0; k < len; ++k) {
-                    const uint64_t x = stage[b + k];
-                    rank += (x < v || (x == v && b + k < q)) ? 1u : 0u;
-                }
-                out = b + rank;
-            }
+            // the code's slots are [cur - len, cur) once placed
+            if (len >= 2 && len <= local_max) out = rank_slot(stage, v, cur[c] - len, len);
             pairs[lo + out] = v;
         }
     } else {
@@ -914,13 +1057,174 @@ __global__ void __launch_bounds__(kSortThreads) TGS_SORT_ATTR group_sort_kernel(
                 const uint32_t p = lo + atomicAdd(&cur[c[j]], 1u);
                 pairs[p] = pr[j];
                 // records exist only with SB == 1, where a code is a segment
-                if (rs.masks && hist[c[j]] == 1u) rs.put((uint32_t)(sbase + c[j]), p, pr[j]);
+                if (rs.masks && hist[c[j]] == 1u) rs.put((uint32_t)(gc.sbase + c[j]), p, pr[j]);
             }
         }
     }
-    if (tile_hist) {
+}
+
+// ---- split groups ------------------------------------------------------------
+// A long group is cut into parts in passes over its entries, and the parts are
+// sorted one per workgroup:
+//   slices (group_sort_kernel)  entries per code of every slice of kSlice
+//                               entries, added to the group's hist;
+//   group_split_kernel          one workgroup per slice: the parts follow from
+//                               the complete hist, the slice's entries are
+//                               ordered by part in LDS and written to the
+//                               parts' places in runs;
+//   sort_small_kernel           one workgroup per part: bucket sort in LDS.
+// The numbers of slices and parts are known on the device only, so their
+// workgroups stride over the lists; the grids are what the 256 CUs hold (an
+// upper bound as the grid would launch thousands of empty workgroups, at over
+// a microsecond each and CU).
+constexpr int kSplitThreads = 512;
+constexpr int kSplitGrid = 512;  // two workgroups per CU (LDS)
+
+struct SplitLds {
+    union {
+        uint64_t stage[kSlice];
+        uint32_t pre[kMaxGroupSegs];  // exclusive prefix of the code counts (before the staging)
+    };
+    uint16_t code[kSlice];
+    uint32_t part[kMaxGroupSegs];  // part | tile of the group << kPartBits of each code
+    uint32_t begin[kMaxParts];     // first entry of the part, relative to the group; then its place for this slice
+    union {
+        uint32_t count[kMaxParts];      // first code; then the slice's entries per part and their exclusive prefix
+        uint32_t tail[kSplitThreads];   // each thread's last code count
+    };
+};
+constexpr int kPartBits = 11;
+static_assert(1 << kPartBits == kMaxParts, "part numbers");
+
+__global__ void __launch_bounds__(kSplitThreads) group_split_kernel(
+    const uint64_t* __restrict__ tmp_pair, const uint16_t* __restrict__ tmp_code, const uint32_t* __restrict__ group_off,
+    GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* __restrict__ pairs, uint16_t* __restrict__ part_tile,
+    uint32_t* __restrict__ bin_off, const int64_t* __restrict__ counters, uint8_t* __restrict__ repaired,
+    uint32_t* __restrict__ queued, uint32_t* __restrict__ tile_count, GroupSplit sp) {
+    constexpr int NT = kSplitThreads;
+    constexpr int kPer = kMaxGroupSegs / NT;  // codes per thread
+    constexpr int kEnt = kSlice / NT;         // entries per thread
+    constexpr int kPpt = kMaxParts / NT;      // parts per thread
+    __shared__ SplitLds L;
+    __shared__ uint32_t lds32[NT / kWave];
+    __shared__ uint32_t unit0;
+    uint4 next = sp.list[blockIdx.x];  // (the grid is at most the list's length)
+    const uint32_t slices = sp.ctl[1];
+    for (uint32_t it = blockIdx.x; it < slices; it += gridDim.x) {
+        const uint4 sl = next;
+        if (it + gridDim.x < slices) next = sp.list[it + gridDim.x];
+        const int g = (int)sl.x;
+        uint32_t* gh = sp.hist + (int64_t)sl.y * sp.stride;
+        uint32_t* cursor = gh + sp.stride - kMaxParts;
+        const uint32_t lo = (uint32_t)min((int64_t)group_off[g], capacity);
+        const uint32_t n = (uint32_t)min((int64_t)group_off[g + 1], capacity) - lo;
+        const GroupCodes gc = codes_of(gm, g, nseg);
+        // the slice's entries, requested before the prefix is worked out
+        uint32_t c[kEnt];
+        uint64_t pr[kEnt];
+#pragma unroll
+        for (int j = 0; j < kEnt; ++j) {
+            const uint32_t e = min(sl.z + (uint32_t)(j * NT) + threadIdx.x, sl.w - 1);
+            c[j] = tmp_code[e];
+            pr[j] = tmp_pair[e];
+        }
+        uint32_t cnt[kPer], s = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int k = (int)threadIdx.x * kPer + j;
+            cnt[j] = k < gc.codes ? gh[k] : 0u;
+            s += cnt[j];
+        }
+        uint32_t total;
+        const uint32_t before = block_excl_u32<NT>(s, lds32, &total);
+        uint32_t run = before;
+        // last count of the thread before, for its last code's length
+        L.tail[threadIdx.x] = cnt[kPer - 1];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            L.pre[threadIdx.x * kPer + j] = run;
+            run += cnt[j];
+        }
         __syncthreads();
-        if (threadIdx.x < kTileBuckets && thist[threadIdx.x]) atomicAdd(&tile_hist[threadIdx.x], thist[threadIdx.x]);
+        uint32_t flag[kPer];
+        const uint32_t flags = part_starts(cnt, before, threadIdx.x ? L.tail[threadIdx.x - 1] : 0u, gc.codes, flag);
+        uint32_t nflags;
+        uint32_t p = block_excl_u32<NT>(flags, lds32, &nflags);
+        const uint32_t parts = nflags + 1;  // <= kMaxParts, see split_group
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int k = (int)threadIdx.x * kPer + j;
+            p += flag[j];
+            if (k < gc.codes) {
+                L.part[k] = p | tile_of_code(gm, gc, g, (uint32_t)k) << kPartBits;
+                if (flag[j] || k == 0) {
+                    L.begin[p] = L.pre[k];
+                    L.count[p] = (uint32_t)k;  // first code, for the unit list
+                }
+            }
+        }
+        __syncthreads();
+        if (sl.z == lo) {
+            // the group's first slice: its results and its parts
+            if (threadIdx.x == 0) unit0 = atomicAdd(&sp.ctl[2], parts);
+            group_results<NT>(gm, gc, g, lo, n, L.pre, counters[2] == 0, bin_off, repaired, queued, tile_count, lds32);
+            __syncthreads();
+            for (uint32_t q = threadIdx.x; q < parts; q += NT) {
+                const uint32_t b = L.begin[q], e = q + 1 < parts ? L.begin[q + 1] : n;
+                const uint32_t k0 = L.count[q], k1 = q + 1 < parts ? L.count[q + 1] : (uint32_t)gc.codes;
+                const uint32_t ta = tile_of_code(gm, gc, g, k0);
+                sp.units[unit0 + q] = make_uint4(lo + b, e - b, ta, tile_of_code(gm, gc, g, k1 - 1) - ta + 1);
+            }
+            __syncthreads();
+        }
+        for (uint32_t q = threadIdx.x; q < parts; q += NT) L.count[q] = 0;
+        __syncthreads();
+        uint32_t rank[kEnt], pt[kEnt];
+#pragma unroll
+        for (int j = 0; j < kEnt; ++j) {
+            const bool ok = sl.z + (uint32_t)(j * NT) + threadIdx.x < sl.w;
+            pt[j] = L.part[c[j]] & (kMaxParts - 1);
+            rank[j] = ok ? atomicAdd(&L.count[pt[j]], 1u) : 0u;
+        }
+        __syncthreads();
+        // exclusive prefix over the parts, and each part's place in the output
+        uint32_t pc[kPpt], ps = 0;
+#pragma unroll
+        for (int j = 0; j < kPpt; ++j) {
+            const uint32_t q = threadIdx.x * kPpt + j;
+            pc[j] = q < parts ? L.count[q] : 0u;
+            ps += pc[j];
+        }
+        uint32_t base[kPpt];
+#pragma unroll
+        for (int j = 0; j < kPpt; ++j) base[j] = pc[j] ? atomicAdd(&cursor[threadIdx.x * kPpt + j], pc[j]) : 0u;
+        uint32_t pex = block_excl_u32<NT>(ps, lds32, &total);
+#pragma unroll
+        for (int j = 0; j < kPpt; ++j) {
+            const uint32_t q = threadIdx.x * kPpt + j;
+            if (q < parts) {
+                L.count[q] = pex;
+                L.begin[q] += base[j] - pex;  // slot i of the slice goes to begin + i
+            }
+            pex += pc[j];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kEnt; ++j) {
+            if (sl.z + (uint32_t)(j * NT) + threadIdx.x >= sl.w) continue;
+            const uint32_t i = L.count[pt[j]] + rank[j];
+            L.stage[i] = pr[j];
+            L.code[i] = (uint16_t)c[j];
+        }
+        __syncthreads();
+        const uint32_t m = sl.w - sl.z;
+        for (uint32_t i = threadIdx.x; i < m; i += NT) {
+            const uint32_t k = L.part[L.code[i]];
+            const uint32_t to = lo + L.begin[k & (kMaxParts - 1)] + i;
+            pairs[to] = L.stage[i];
+            part_tile[to] = (uint16_t)(k >> kPartBits);
+        }
+        __syncthreads();
     }
 }
 
@@ -970,19 +1274,25 @@ hipError_t launch_repair_select(const uint32_t* bin_off, int64_t T, int K, float
 }
 
 hipError_t launch_group_scan(const uint32_t* gcount, GroupMap gm, uint32_t* group_off, uint32_t* order,
-                             hipStream_t s) {
-    hipLaunchKernelGGL(group_scan_kernel, dim3(1), dim3(kTailThreads), 0, s, gcount, gm, group_off, order);
+                             int64_t capacity, const GroupSplit& sp, hipStream_t s) {
+    hipLaunchKernelGGL(group_scan_kernel, dim3(1), dim3(kTailThreads), 0, s, gcount, gm, group_off, order, capacity, sp);
     return hipGetLastError();
 }
 
 hipError_t launch_group_sort(const uint64_t* tmp_pair, const uint16_t* tmp_code, const uint32_t* group_off,
                              const uint32_t* order, GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* pairs, uint32_t* bin_off,
                              uint32_t* lists, int64_t list_stride, uint32_t* bucket_count,
-                             int64_t* counters, bool queue_all, uint8_t* repaired, RecordSink rs,
-                             uint32_t* tile_hist, hipStream_t s) {
-    hipLaunchKernelGGL(group_sort_kernel, dim3((unsigned)gm.G), dim3(kSortThreads), 0, s, tmp_pair, tmp_code, group_off, order, gm,
-                       nseg, capacity, pairs, bin_off, lists, list_stride, bucket_count, counters, queue_all, repaired,
-                       rs, tile_hist);
+                             const int64_t* counters, bool queue_all, uint8_t* repaired, RecordSink rs,
+                             uint32_t* queued, uint32_t* tile_count, const GroupSplit& sp, uint16_t* part_tile,
+                             hipStream_t s) {
+    hipLaunchKernelGGL(group_sort_kernel, dim3((unsigned)(sp.slice_grid + gm.G)), dim3(kSortThreads), 0, s, tmp_pair,
+                       tmp_code, group_off, order, gm, nseg, capacity, pairs, bin_off, lists, list_stride, bucket_count,
+                       counters, queue_all, repaired, rs, queued, tile_count, sp);
+    if (sp.list) {
+        hipLaunchKernelGGL(group_split_kernel, dim3((unsigned)std::min(sp.max_slices, kSplitGrid)),
+                           dim3(kSplitThreads), 0, s, tmp_pair, tmp_code, group_off, gm, nseg, capacity, pairs,
+                           part_tile, bin_off, counters, repaired, queued, tile_count, sp);
+    }
     return hipGetLastError();
 }
 

@@ -1,5 +1,6 @@
-// Wavefront sorting networks over 64-bit keys (unique keys; the maximum key
-// pads): used by the repair sorts of the (tile, bin) segments.
+// Sorts of 64-bit keys (unique keys; the maximum key pads) used by the repair
+// of the (tile, bin) segments: wavefront and workgroup bitonic networks, and a
+// workgroup bucket sort.
 #pragma once
 
 #include "common.hpp"
@@ -161,6 +162,123 @@ __device__ __forceinline__ void sort_block_reg(uint64_t (&v)[E], uint64_t* lds) 
             }
         }
     }
+}
+
+// ---- workgroup bucket sort -----------------------------------------------------
+// n <= CAP keys in registers (key j NT + t in register j of thread t) are
+// counting-sorted into kBucketSlots buckets in LDS; a key's place inside its
+// bucket is its rank there. With the buckets spread over the keys' own range a
+// bucket holds one or two keys, so this is one LDS atomic, one LDS write and a
+// few LDS reads per key against the O(log^2) exchanges of the networks.
+constexpr int kBucketSlots = 4096;
+constexpr int kBucketRank = 512;  // longest bucket ordered by rank
+
+template <int NT, int CAP>
+struct BucketLds {
+    uint32_t off[kBucketSlots + 1];  // first slot of each bucket
+    uint16_t bucket[CAP];            // bucket of each slot
+    uint32_t sum[NT / kWave], lo[NT / kWave], hi[NT / kWave];
+    uint64_t stage[CAP + 4];
+};
+
+// Buckets of the keys by (tile, upper word): the slots are divided evenly
+// among the `tiles` tiles (b[j] holds the key's tile, 0 .. tiles - 1 <
+// kBucketSlots, on entry), and within a tile spread by a monotone map over the
+// range of all keys' upper words. Every register holds a key (repeated ones
+// past the last).
+template <int E, int NT, int CAP>
+__device__ __forceinline__ void range_buckets(const uint64_t (&key)[E], uint32_t (&b)[E], uint32_t tiles,
+                                              BucketLds<NT, CAP>& L) {
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+        lo = min(lo, (uint32_t)(key[j] >> 32));
+        hi = max(hi, (uint32_t)(key[j] >> 32));
+    }
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) {
+        lo = min(lo, xor_lane_u32(lo, m));
+        hi = max(hi, xor_lane_u32(hi, m));
+    }
+    if (lane() == 0) {
+        L.lo[threadIdx.x / kWave] = lo;
+        L.hi[threadIdx.x / kWave] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NT / kWave; ++i) {
+        lo = min(lo, L.lo[i]);
+        hi = max(hi, L.hi[i]);
+    }
+    const uint32_t span = hi - lo, slots = kBucketSlots / tiles;
+    // floor(2^32 slots / (span + 1)) without a 64-bit division; any smaller
+    // value gives a monotone map too
+    const uint32_t mul = span < slots ? 0u : (uint32_t)((float)slots * (4294967296.0f * 0.999999f) / ((float)span + 1.0f));
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+        const uint32_t d = (uint32_t)(key[j] >> 32) - lo;
+        b[j] = b[j] * slots + (mul ? __umulhi(d, mul) : d);
+    }
+}
+
+// Places the keys in L.stage by bucket (L.off, L.bucket follow; ends with a
+// barrier) and returns whether some bucket has more than kBucketRank keys. L.off
+// must not be in use by another wavefront when this is called.
+template <int E, int NT, int CAP>
+__device__ __forceinline__ bool place_buckets(const uint64_t (&key)[E], const uint32_t (&b)[E], uint32_t n,
+                                              BucketLds<NT, CAP>& L) {
+    constexpr int kPer = kBucketSlots / NT;
+    for (int k = threadIdx.x; k < kBucketSlots; k += NT) L.off[k] = 0;
+    __syncthreads();
+    uint32_t rank[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j)
+        rank[j] = (uint32_t)(j * NT) + threadIdx.x < n ? atomicAdd(&L.off[b[j]], 1u) : 0u;
+    __syncthreads();
+    uint32_t c[kPer], s = 0, longest = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        c[j] = L.off[threadIdx.x * kPer + j];
+        s += c[j];
+        longest = max(longest, c[j]);
+    }
+    const uint32_t incl = wave_inclusive_sum(s);
+    if (lane() == kWave - 1) L.sum[threadIdx.x / kWave] = incl;
+    __syncthreads();
+    uint32_t run = incl - s;
+#pragma unroll
+    for (int i = 0; i < NT / kWave; ++i) run += i < (int)(threadIdx.x / kWave) ? L.sum[i] : 0u;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        L.off[threadIdx.x * kPer + j] = run;
+        run += c[j];
+    }
+    if (threadIdx.x == 0) L.off[kBucketSlots] = n;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+        if ((uint32_t)(j * NT) + threadIdx.x >= n) continue;
+        const uint32_t q = L.off[b[j]] + rank[j];
+        L.stage[q] = key[j];
+        L.bucket[q] = (uint16_t)b[j];
+    }
+    return __syncthreads_or(longest > (uint32_t)kBucketRank) != 0;
+}
+
+// Place of the key v within its bucket [b, b + len) of the stage: its rank
+// among the bucket's (unique) keys. Four keys are read at a time, so that
+// their LDS latencies overlap (the stage has kRankPad slots past its end).
+constexpr int kRankPad = 4;
+__device__ __forceinline__ uint32_t rank_slot(const uint64_t* stage, uint64_t v, uint32_t b, uint32_t len) {
+    uint32_t rank = 0;
+    for (uint32_t k = 0; k < len; k += kRankPad) {
+        uint64_t x[kRankPad];
+#pragma unroll
+        for (uint32_t i = 0; i < kRankPad; ++i) x[i] = stage[b + k + i];
+#pragma unroll
+        for (uint32_t i = 0; i < kRankPad; ++i) rank += (k + i < len && x[i] < v) ? 1u : 0u;
+    }
+    return b + rank;
 }
 
 }  // namespace tgs

@@ -1,0 +1,134 @@
+"""Groups of more than 16384 entries are split over the chip: slices of 4096
+entries are ordered by part first, then one workgroup sorts each part. Streams,
+bin offsets, repair flags, the repaired-entry count and the tile order
+bit-exact against the oracle's schedule at the edges: just above the group
+sort's stage (4096), the longest group that is not split and one entry more,
+whole and ragged slices, a sub-segment that is a part by itself (more than 2048
+entries) up to and past the workgroup sort (8192), buckets of 512 and 513 equal
+depths, narrow depth clusters inside one sub-bin, the longest group that is
+split and one entry more, several groups, per-tile bin counts, the capacity from
+which on groups are split, and a truncated stream."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import scenes
+
+pytestmark = pytest.mark.gpu
+
+tg = pytest.importorskip("paper_2609_03613_amd")
+
+SPLIT_MAX = 682 * 2048  # the longest group that is split
+
+
+def to_np(t):
+    return t.detach().cpu().numpy()
+
+
+def scene(n, W, clusters, seed, tiles=None):
+    """n entries on the one row of tiles of a W x 16 image, depth U[2, 20];
+    clusters: (entries, tile, depth, relative spread) at the front."""
+    rng = np.random.default_rng(seed)
+    tx = (W + 15) // 16
+    depth = rng.uniform(2.0, 20.0, n).astype(np.float32)
+    tile = rng.integers(0, tiles or tx, n)
+    at = 0
+    for size, t, z, spread in clusters:
+        depth[at:at + size] = (z * (1.0 + spread * rng.random(size))).astype(np.float32)
+        tile[at:at + size] = t
+        at += size
+    perm = rng.permutation(n)
+    depth, tile = depth[perm], tile[perm]
+    rect = np.stack([tile, np.zeros(n, np.int64), tile + 1, np.ones(n, np.int64)], 1)
+    return depth, rect
+
+
+def bin_of(depth, rect, W, params, capacity=None, sync=True):
+    dev = torch.device("cuda:0")
+    cam = scenes.camera(np.eye(3), np.zeros(3), 100.0, 100.0, W / 2, 8.0, W, 16)
+    s = torch.zeros((len(depth), 16), dtype=torch.float32, device=dev)
+    i = torch.as_tensor(scenes.make_info(depth, rect).view(np.int32)).to(dev)
+    b = tg.Renderer(cam, params, device=dev).bin(s, i, "binned", capacity=capacity, sync=sync)
+    torch.cuda.synchronize()
+    return b
+
+
+CASES = [
+    # n, W, clusters, tiles used (None: all)
+    (4097, 128, (), None),
+    (8192, 128, ((4000, 2, 5.0, 0.3),), None),
+    (8193, 128, (), 1),
+    (16384, 128, ((1000, 1, 5.0, 0.0),), None),
+    (16385, 128, ((1000, 1, 5.0, 0.0), (513, 2, 6.0, 0.0), (512, 2, 7.0, 0.0)), None),
+    (36864, 128, ((2049, 3, 7.0, 0.0), (2048, 3, 9.0, 0.0)), None),
+    (40001, 128, ((4096, 1, 7.0, 0.0), (4097, 1, 9.0, 0.0), (200, 0, 3.0, 0.0)), None),
+    (50000, 128, ((8193, 7, 7.0, 0.0), (3000, 6, 8.0, 1e-4), (5000, 5, 8.0, 2e-6)), 8),
+    (20000, 128, ((2049, 3, 7.0, 0.0), (2048, 3, 9.0, 0.0)), None),     # over-long and longest ordinary code
+    (20000, 128, ((4096, 1, 7.0, 0.0), (4097, 1, 9.0, 0.0), (200, 0, 3.0, 0.0)), None),
+    (30000, 128, ((8193, 7, 7.0, 0.0), (3000, 6, 8.0, 1e-4), (5000, 5, 8.0, 2e-6)), None),
+    (40000, 128, ((30000, 4, 10.0, 1e-3),), None),                       # a surface: one narrow depth range
+    (60000, 300, ((20000, 2, 6.0, 0.01), (20000, 15, 9.0, 0.01)), None),  # three groups, the last of 3 tiles
+    (SPLIT_MAX, 128, (), None),
+    (SPLIT_MAX + 1, 128, (), None),
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_split_groups_bit_exact(case):
+    n, W, clusters, tiles = CASES[case]
+    depth, rect = scene(n, W, clusters, case, tiles)
+    tx = (W + 15) // 16
+    for K, sub in ((64, 0), (64, 2), (24, 0)):
+        ref = oracle.schedule(depth, rect, tx, 1, K=K, znear=0.01, zfar=1e10)
+        b = bin_of(depth, rect, W, tg.Params(num_bins=K, sub_bins=sub))
+        assert b.num_entries == n == ref["M"]
+        off = to_np(b.offsets).view(np.uint32)
+        assert np.array_equal(off, ref["bin_offsets"]), (K, sub)
+        assert np.array_equal(to_np(b.pairs)[:n].view(np.uint64), ref["stream"]), (K, sub)
+        seg = np.diff(off.astype(np.int64))
+        assert np.array_equal(to_np(b.repaired)[:len(seg)], (seg >= 2).astype(np.uint8))
+        assert to_np(b.counters).tolist() == [n, n, 0, int(seg[seg >= 2].sum())]
+        cnt = np.diff(off[::K].astype(np.int64))
+        order = to_np(b.dispatch_order())
+        assert np.array_equal(np.sort(order), np.arange(tx))
+        bits = np.array([int(c).bit_length() for c in cnt[order]])
+        assert (np.diff(bits) <= 0).all()
+
+
+@pytest.mark.parametrize("case", [3, 7, 9, 10, 12])
+def test_split_groups_per_tile_bins(case):
+    n, W, clusters, tiles = CASES[case]
+    depth, rect = scene(n, W, clusters, case, tiles)
+    tx = (W + 15) // 16
+    kt = np.random.default_rng(case).choice([1, 2, 16, 64, 256], size=tx).astype(np.int32)
+    ref = oracle.schedule_tiles(depth, rect, tx, 1, kt, znear=0.01, zfar=1e10)
+    dev = torch.device("cuda:0")
+    b = bin_of(depth, rect, W, tg.Params(num_bins=256, per_tile_bins=torch.as_tensor(kt).to(dev)))
+    S = int(ref["seg_base"][-1])
+    assert np.array_equal(to_np(b.offsets).view(np.uint32)[:S + 1], ref["bin_offsets"])
+    assert np.array_equal(to_np(b.pairs)[:n].view(np.uint64), ref["stream"])
+
+
+def test_truncated_stream_of_a_split_group():
+    # more entries than the buffers hold, without a host count: flagged, and
+    # the capacity's worth of entries are some of the input's
+    n = 50000
+    depth, rect = scene(n, 128, ((20000, 2, 6.0, 0.0),), 3)
+    b = bin_of(depth, rect, 128, tg.Params(), capacity=30001, sync=False)
+    c = to_np(b.counters)
+    assert c[0] == n and c[2] == 1 and c[3] == 0
+    ids = to_np(b.pairs).view(np.uint64)[:30001] & np.uint64(0xFFFFFFFF)
+    assert len(np.unique(ids)) == 30001 and ids.max() < n
+
+
+@pytest.mark.parametrize("capacity", [32768, 32769])
+@pytest.mark.parametrize("sub", [2, 8])
+def test_same_stream_on_both_sides_of_the_capacity_rule(capacity, sub):
+    # eight groups of eight tiles: split from 8 x 4096 entries of capacity on
+    n, W = 30000, 1024
+    depth, rect = scene(n, W, ((17000, 3, 6.0, 0.2), (3000, 4, 7.0, 1e-5)), 5)
+    ref = oracle.schedule(depth, rect, W // 16, 1, K=64, znear=0.01, zfar=1e10)
+    b = bin_of(depth, rect, W, tg.Params(sub_bins=sub), capacity=capacity)
+    assert np.array_equal(to_np(b.offsets).view(np.uint32), ref["bin_offsets"])
+    assert np.array_equal(to_np(b.pairs)[:n].view(np.uint64), ref["stream"])
