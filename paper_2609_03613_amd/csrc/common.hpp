@@ -213,6 +213,7 @@ struct RecordSink {
 // SB + code.
 struct GroupMap {
     int K, GT, G, GS, SB;
+    uint32_t GT_mul;  // ceil(2^32 / GT), or 0
     int64_t T;
     const uint32_t* seg_base;
     const uint2* tile_seg;

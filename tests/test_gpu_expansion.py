@@ -1,0 +1,117 @@
+"""The expansion of Gaussians into (Gaussian, tile) entries at its edges:
+rectangles of every width from one tile to a whole row, single tiles, whole
+images, wavefronts of 64 Gaussians with no, one and all entries, runs of empty
+Gaussians, entry counts around the rounds of 64 and the steps of 256, group
+sizes that are and are not powers of two, and a grid of more than 2^20 tiles
+(where the row comes from an integer division). Every tile's stream against the
+rectangles expanded by numpy: whole numbers, equal."""
+import numpy as np
+import pytest
+import torch
+
+import scenes
+
+pytestmark = pytest.mark.gpu
+
+tg = pytest.importorskip("paper_2609_03613_amd")
+
+
+def expected(depth, rect, tx):
+    """(tile, pair) of every entry, by tile and pair."""
+    tiles, pairs = [], []
+    bits = depth.view(np.uint32).astype(np.uint64)
+    for g, (x0, y0, x1, y1) in enumerate(rect):
+        if x1 <= x0 or y1 <= y0:
+            continue
+        t = (np.arange(y0, y1)[:, None] * tx + np.arange(x0, x1)[None, :]).ravel()
+        tiles.append(t)
+        pairs.append(np.full(len(t), (bits[g] << np.uint64(32)) | np.uint64(g), np.uint64))
+    if not tiles:
+        return np.zeros(0, np.int64), np.zeros(0, np.uint64)
+    tiles, pairs = np.concatenate(tiles), np.concatenate(pairs)
+    o = np.lexsort((pairs, tiles))
+    return tiles[o], pairs[o]
+
+
+def widths(tx, ty):
+    """One Gaussian per width, at both ends of the row, of 1 to 5 rows."""
+    out = []
+    for w in range(1, tx + 1):
+        h = 1 + w % min(5, ty)
+        y = (7 * w) % (ty - h + 1)
+        out += [(0, y, w, y + h), (tx - w, y, tx, y + h)]
+    return out
+
+
+def counts(tx, ty):
+    """64-Gaussian wavefronts of 0, 1, 63..65, 255..257 and 511..513 entries, with
+    the entries in one Gaussian and one to a Gaussian."""
+    out = []
+    for m in (0, 1, 63, 64, 65, 255, 256, 257, 511, 512, 513):
+        one = [(0, 0, 0, 0)] * 64
+        rows, rest = divmod(m, tx)
+        if rows:
+            one[5] = (0, 0, tx, rows)
+        if rest:
+            one[63] = (0, 1, rest, 2)
+        out += one
+        if m <= 64:
+            out += [(i % tx, 0, i % tx + 1, 1) if i < m else (3, 3, 3, 3) for i in range(64)]
+    return out
+
+
+def mixed(tx, ty, n, seed):
+    rng = np.random.default_rng(seed)
+    x0, y0 = rng.integers(0, tx, n), rng.integers(0, ty, n)
+    w, h = rng.geometric(0.3, n), rng.geometric(0.3, n)
+    r = np.stack([x0, y0, np.minimum(x0 + w, tx), np.minimum(y0 + h, ty)], 1)
+    r[rng.random(n) < 0.4] = 0
+    r[n // 2] = (0, 0, tx, ty)
+    return [tuple(int(v) for v in q) for q in r]
+
+
+CASES = {
+    "widths 113x9": (113, 9, 16, lambda tx, ty: widths(tx, ty)),
+    "counts 32x40": (32, 40, 16, lambda tx, ty: counts(tx, ty)),
+    "mixed 37x29": (37, 29, 8, lambda tx, ty: mixed(tx, ty, 3000, 1)),
+    "mixed 1x1": (1, 1, 32, lambda tx, ty: mixed(tx, ty, 130, 2)),
+    "no entries": (8, 8, 16, lambda tx, ty: [(0, 0, 0, 0)] * 100),
+    "2048x520 tiles": (2048, 520, 8, lambda tx, ty: mixed(tx, ty, 300, 3) + widths(tx, ty)[-300:]),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+@pytest.mark.parametrize("order, K", [("binned", 1), ("binned", 3), ("binned", 64), ("binned", 600), ("binned", 1000),
+                                      ("global", 1), ("per-tile", 4)])
+def test_expansion(name, order, K):
+    tx, ty, ts, make = CASES[name]
+    if tx * ty > 1 << 20 and K > 64:
+        pytest.skip("tens of GB of segment counters")
+    rect = np.array(make(tx, ty), np.int64).reshape(-1, 4)
+    n = len(rect)
+    depth = np.random.default_rng(n).uniform(1.0, 30.0, n).astype(np.float32)
+    tiles, pairs = expected(depth, rect, tx)
+    W, H = tx * ts, ty * ts
+    dev = torch.device("cuda:0")
+    cam = scenes.camera(np.eye(3), np.zeros(3), 100.0, 100.0, W / 2, H / 2, W, H)
+    kt = None
+    if order == "per-tile":
+        kt = torch.as_tensor(np.random.default_rng(3).choice([1, 2, 4], tx * ty).astype(np.int32)).to(dev)
+    r = tg.Renderer(cam, tg.Params(tile_size=ts, num_bins=K, per_tile_bins=kt), device=dev)
+    s = torch.zeros((n, 16), dtype=torch.float32, device=dev)
+    i = torch.as_tensor(scenes.make_info(depth, rect).view(np.int32)).to(dev)
+    b = r.bin(s, i, "global" if order == "global" else "binned")
+    torch.cuda.synchronize()
+    M = len(pairs)
+    assert b.num_entries == M
+    off = b.offsets.cpu().numpy().view(np.uint32)
+    if order == "global":
+        key = b.keys[:M].cpu().numpy().view(np.uint64)
+        got = (key << np.uint64(32)) | b.vals[:M].cpu().numpy().view(np.uint32).astype(np.uint64)
+        assert np.array_equal(key >> np.uint64(32), tiles.astype(np.uint64))
+        first = off
+    else:
+        got = b.pairs[:M].cpu().numpy().view(np.uint64)
+        first = off[b.seg_base.cpu().numpy()] if order == "per-tile" else off[::K]
+    assert np.array_equal(first, np.searchsorted(tiles, np.arange(tx * ty + 1)))
+    assert np.array_equal(got, pairs)
