@@ -299,8 +299,8 @@ TGS_API size_t tgs_bin_workspace_size(int64_t n, int64_t capacity, const tgs_cam
 /* Builds the entry stream of `order`. num_entries_host: NULL = no host
    synchronisation (an overflow is only reported through counters[2]);
    non-NULL = wait for the entry count, store it there, and return
-   TGS_ERR_CAPACITY when it exceeds capacity (the outputs then hold a
-   truncated stream, and nothing uses them any more). The rest of the BINNED
+   TGS_ERR_CAPACITY without building the stream when it exceeds capacity
+   (nothing uses the outputs any more then). Otherwise the rest of the BINNED
    stream is built behind the call, as without the count. Not under capture.
    GLOBAL order without the host count: the radix sort runs over all
    `capacity` slots, those past the entry count padded with keys past the

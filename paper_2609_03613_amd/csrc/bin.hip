@@ -395,7 +395,9 @@ __global__ void __launch_bounds__(256) bin_count_kernel(const uint4* __restrict_
                                                         const float* __restrict__ zrange, NearKey nk, SegMap sm,
                                                         int tiles_x, int tiles_y, uint32_t* __restrict__ count,
                                                         int64_t nseg,
-                                                        uint32_t* __restrict__ entry_rank, int64_t capacity) {
+                                                        uint32_t* __restrict__ entry_rank, int64_t capacity,
+                                                        const int64_t* __restrict__ stop) {
+    if (stop && stop[2]) return;
     __shared__ WaveGauss wg[4];
     const uint32_t x = (uint32_t)xcc_id() % (uint32_t)kCopies;
     const int64_t S = VAR ? (int64_t)sm.seg_base[(int64_t)tiles_x * tiles_y] : nseg;
@@ -433,7 +435,8 @@ __global__ void __launch_bounds__(256) bin_scatter_kernel(const uint4* __restric
                                                           const uint32_t* __restrict__ base, int64_t nseg,
                                                           const uint32_t* __restrict__ entry_rank,
                                                           uint64_t* __restrict__ pairs, int64_t capacity,
-                                                          RecordSink rs) {
+                                                          RecordSink rs, const int64_t* __restrict__ stop) {
+    if (stop && stop[2]) return;
     __shared__ WaveGauss wg[4];
     const int64_t S = VAR ? (int64_t)sm.seg_base[(int64_t)tiles_x * tiles_y] : nseg;
     constexpr int R = kExpandRounds;
@@ -516,6 +519,7 @@ __global__ void __launch_bounds__(kCountThreads) group_count_kernel(const uint4*
                           ra.zrange, ra.samples, U.r);
         return;
     }
+    if (ra.stop && ra.stop[2]) return;
     const int64_t chunk = blockIdx.x - 1;
     uint32_t* hist = U.c.hist;
     for (int g = threadIdx.x; g < gm.G; g += kCountThreads) hist[g] = 0;
@@ -556,7 +560,8 @@ __global__ void __launch_bounds__(kScatterThreads) group_scatter_kernel(const ui
                                                             const uint32_t* __restrict__ wgbase,
                                                             uint64_t* __restrict__ tmp_pair,
                                                             uint16_t* __restrict__ tmp_code, int64_t capacity,
-                                                            GroupSplit sp) {
+                                                            GroupSplit sp, const int64_t* __restrict__ stop) {
+    if (stop && stop[2]) return;
     constexpr int NT = kScatterThreads, NW = NT / kWave;
     static_assert(kGroupChunk % NT == 0, "whole wavefront slabs per chunk");
     if (sp.list) {
@@ -1155,30 +1160,30 @@ hipError_t launch_depth_range(const uint32_t* info, const uint32_t* vis_ids, con
 
 hipError_t launch_bin_count(const uint32_t* info, int64_t n, const uint32_t* emit_off, const float* zrange,
                             NearKey nk, SegMap sm, int tiles_x, int tiles_y, uint32_t* count, int64_t nseg,
-                            uint32_t* entry_rank, int64_t capacity, hipStream_t s) {
+                            uint32_t* entry_rank, int64_t capacity, const int64_t* stop, hipStream_t s) {
     if (n == 0) return hipSuccess;
     const auto* in = reinterpret_cast<const uint4*>(info);
     if (sm.seg_base)
         hipLaunchKernelGGL(bin_count_kernel<true>, dim3(grid_for(n, 256)), dim3(256), 0, s, in, n, emit_off, zrange,
-                           nk, sm, tiles_x, tiles_y, count, nseg, entry_rank, capacity);
+                           nk, sm, tiles_x, tiles_y, count, nseg, entry_rank, capacity, stop);
     else
         hipLaunchKernelGGL(bin_count_kernel<false>, dim3(grid_for(n, 256)), dim3(256), 0, s, in, n, emit_off, zrange,
-                           nk, sm, tiles_x, tiles_y, count, nseg, entry_rank, capacity);
+                           nk, sm, tiles_x, tiles_y, count, nseg, entry_rank, capacity, stop);
     return hipGetLastError();
 }
 
 hipError_t launch_bin_scatter(const uint32_t* info, int64_t n, const uint32_t* emit_off, const float* zrange,
                               NearKey nk, SegMap sm, int tiles_x, int tiles_y, const uint32_t* bin_off,
                               const uint32_t* base, int64_t nseg, const uint32_t* entry_rank, uint64_t* pairs,
-                              int64_t capacity, RecordSink rs, hipStream_t s) {
+                              int64_t capacity, RecordSink rs, const int64_t* stop, hipStream_t s) {
     if (n == 0) return hipSuccess;
     const auto* in = reinterpret_cast<const uint4*>(info);
     if (sm.seg_base)
         hipLaunchKernelGGL(bin_scatter_kernel<true>, dim3(grid_for(n, 256)), dim3(256), 0, s, in, n, emit_off, zrange,
-                           nk, sm, tiles_x, tiles_y, bin_off, base, nseg, entry_rank, pairs, capacity, rs);
+                           nk, sm, tiles_x, tiles_y, bin_off, base, nseg, entry_rank, pairs, capacity, rs, stop);
     else
         hipLaunchKernelGGL(bin_scatter_kernel<false>, dim3(grid_for(n, 256)), dim3(256), 0, s, in, n, emit_off,
-                           zrange, nk, sm, tiles_x, tiles_y, bin_off, base, nseg, entry_rank, pairs, capacity, rs);
+                           zrange, nk, sm, tiles_x, tiles_y, bin_off, base, nseg, entry_rank, pairs, capacity, rs, stop);
     return hipGetLastError();
 }
 
@@ -1263,17 +1268,17 @@ hipError_t launch_group_count(const uint32_t* info, int64_t n, const uint32_t* e
 hipError_t launch_group_scatter(const uint32_t* info, int64_t n, const uint32_t* emit_off, const float* zrange,
                                 NearKey nk, GroupMap gm, int tiles_x, int tiles_y, const uint32_t* group_off,
                                 const uint32_t* wgbase, uint64_t* tmp_pair, uint16_t* tmp_code, int64_t capacity,
-                                const GroupSplit& sp, hipStream_t s) {
+                                const GroupSplit& sp, const int64_t* stop, hipStream_t s) {
     if (n == 0) return hipSuccess;
     const int64_t blocks = (n + kGroupChunk - 1) / kGroupChunk;
     if (gm.seg_base)
         hipLaunchKernelGGL(group_scatter_kernel<true>, dim3((unsigned)blocks), dim3(kScatterThreads), 0, s,
                            reinterpret_cast<const uint4*>(info), n, emit_off, zrange, nk, gm, tiles_x, tiles_y,
-                           group_off, wgbase, tmp_pair, tmp_code, capacity, sp);
+                           group_off, wgbase, tmp_pair, tmp_code, capacity, sp, stop);
     else
         hipLaunchKernelGGL(group_scatter_kernel<false>, dim3((unsigned)blocks), dim3(kScatterThreads), 0, s,
                            reinterpret_cast<const uint4*>(info), n, emit_off, zrange, nk, gm, tiles_x, tiles_y,
-                           group_off, wgbase, tmp_pair, tmp_code, capacity, sp);
+                           group_off, wgbase, tmp_pair, tmp_code, capacity, sp, stop);
     return hipGetLastError();
 }
 

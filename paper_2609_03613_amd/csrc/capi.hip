@@ -505,8 +505,9 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
     // for in between, the device idled for 33 us until the host had come back
     // and launched the next kernel (a frame of 2 thousand Gaussians on 128x128
     // 128 us, now 75; of one million on 1920x1080 385 us, now 352). When the
-    // entries exceed the capacity, what was launched meanwhile has built a
-    // truncated stream (as without the host count) and is waited for.
+    // entries exceed the capacity, the kernels that expand them return at once
+    // (stop), the stream that was launched meanwhile is empty and waited for.
+    const int64_t* stop = num_entries_host ? out->counters_dev : nullptr;
     auto read_count = [&]() -> tgs_status {
         if (!num_entries_host) return TGS_OK;
         TGS_HIP(read.wait(M), "read entry count");
@@ -574,7 +575,7 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
         uint16_t* tmp_code = (uint16_t*)(w + L.tmp_code);
         uint32_t* group_order = (uint32_t*)(w + L.group_order);
         const RangeArgs ra{vis_ids, out->counters_dev, nk, S, params->p_lo, params->p_hi, params->pad, zn, zf,
-                           out->zrange_dev, (uint32_t*)(w + L.samples)};
+                           out->zrange_dev, (uint32_t*)(w + L.samples), stop};
         TGS_HIP(launch_group_count(pr->info_dev, n, emit_off, gm, tiles_x, tiles_y, gcount, wgbase, ra, s),
                 "depth range and group count");
         GroupSplit sp = L.sp;
@@ -586,7 +587,7 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
         }
         TGS_HIP(launch_group_scan(gcount, gm, group_off, group_order, cap, sp, s), "group scan");
         TGS_HIP(launch_group_scatter(pr->info_dev, n, emit_off, out->zrange_dev, nk, gm, tiles_x, tiles_y, group_off,
-                                     wgbase, tmp_pair, tmp_code, cap, sp, s),
+                                     wgbase, tmp_pair, tmp_code, cap, sp, stop, s),
                 "group scatter");
         // the group sort leaves the entries per tile; the tile order's placement
         // rides on the repair's long-segment launch. Past kCountedTiles the
@@ -624,7 +625,7 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
                                params->pad, zn, zf, out->zrange_dev, (uint32_t*)(w + L.samples), s),
             "depth range");
     TGS_HIP(launch_bin_count(pr->info_dev, n, emit_off, out->zrange_dev, nk, sm, tiles_x, tiles_y, count, nseg,
-                             entry_rank, cap, s),
+                             entry_rank, cap, stop, s),
             "bin count");
     TGS_HIP(launch_bin_offsets(count, nseg, nseg_dev, out->offsets_dev, zero + kTicketBins,
                                (uint64_t*)(zero + L.status_bins), seg_lists, bucket_count, out->counters_dev,
@@ -636,7 +637,7 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
                                      out->counters_dev, out->repaired_dev, s),
                 "repair selection");
     TGS_HIP(launch_bin_scatter(pr->info_dev, n, emit_off, out->zrange_dev, nk, sm, tiles_x, tiles_y, out->offsets_dev,
-                               count, nseg, entry_rank, out->pairs_dev, cap, rs, s),
+                               count, nseg, entry_rank, out->pairs_dev, cap, rs, stop, s),
             "bin scatter");
     if (params->repair != TGS_REPAIR_NONE)
         TGS_HIP(launch_repair(out->offsets_dev, nseg, out->pairs_dev, seg_lists, bucket_count, rs, false, TileOrder{},

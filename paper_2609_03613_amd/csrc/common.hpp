@@ -363,6 +363,7 @@ struct RangeArgs {
     float p_lo, p_hi, pad, znear, zfar;
     float* zrange;
     uint32_t* samples;  // [S] scratch for the gathered sample keys
+    const int64_t* stop;
 };
 
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
@@ -372,7 +373,8 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 // its copy, with the copy index in the top three bits, goes to entry_rank.
 hipError_t launch_bin_count(const uint32_t* info, int64_t n, const uint32_t* emit_off, const float* zrange,
                             NearKey nk, SegMap sm, int tiles_x, int tiles_y, uint32_t* count, int64_t nseg,
-                            uint32_t* entry_rank, int64_t capacity, hipStream_t s);
+                            uint32_t* entry_rank, int64_t capacity, const int64_t* stop,
+                            hipStream_t s);
 // Repair length buckets: 2..8, 9..16, 17..32, 33..64 (lane groups of one
 // wavefront, registers), 65..512 (one wavefront, LDS), 513..4096 and
 // 4097..8192 (one workgroup, LDS), above 8192 (one workgroup, global memory).
@@ -414,7 +416,7 @@ hipError_t launch_repair_select(const uint32_t* bin_off, int64_t T, int K, float
 hipError_t launch_bin_scatter(const uint32_t* info, int64_t n, const uint32_t* emit_off, const float* zrange,
                               NearKey nk, SegMap sm, int tiles_x, int tiles_y, const uint32_t* bin_off,
                               const uint32_t* base, int64_t nseg, const uint32_t* entry_rank, uint64_t* pairs,
-                              int64_t capacity, RecordSink rs, hipStream_t s);
+                              int64_t capacity, RecordSink rs, const int64_t* stop, hipStream_t s);
 
 // Grouped binning, see GroupMap. group_count: gcount [G] must be zero;
 // wgbase [ceil(n / kGroupChunk) x G] receives each workgroup's slice base
@@ -444,7 +446,7 @@ hipError_t launch_group_scan(const uint32_t* gcount, GroupMap gm, uint32_t* grou
 hipError_t launch_group_scatter(const uint32_t* info, int64_t n, const uint32_t* emit_off, const float* zrange,
                                 NearKey nk, GroupMap gm, int tiles_x, int tiles_y, const uint32_t* group_off,
                                 const uint32_t* wgbase, uint64_t* tmp_pair, uint16_t* tmp_code, int64_t capacity,
-                                const GroupSplit& sp, hipStream_t s);
+                                const GroupSplit& sp, const int64_t* stop, hipStream_t s);
 hipError_t launch_group_sort(const uint64_t* tmp_pair, const uint16_t* tmp_code, const uint32_t* group_off,
                              const uint32_t* order, GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* pairs, uint32_t* bin_off,
                              uint32_t* lists, int64_t list_stride, uint32_t* bucket_count,
