@@ -474,7 +474,7 @@ __global__ void __launch_bounds__(256) bin_scatter_kernel(const uint4* __restric
 // grouped binning (uniform K): the same count / scan / scatter, done in two
 // levels so that no per-entry global atomic is needed. Groups are runs of
 // GT consecutive tiles, i.e. contiguous ranges of GS = GT K segments.
-//   group_count    each workgroup expands the entries of kGroupChunk
+//   group_count    each workgroup expands the entries of gm.chunk
 //                  Gaussians, counts them per group in LDS and reserves its
 //                  slice of every group it touches with one global atomic
 //                  per (workgroup, group): wgbase[wg][g];
@@ -504,7 +504,7 @@ struct CountLds {
 };
 
 // Workgroup 0: the depth range. Workgroups 1..: the group count of chunk
-// blockIdx.x - 1 (kGroupChunk Gaussians, 16 wavefronts).
+// blockIdx.x - 1 (gm.chunk Gaussians, 16 wavefronts).
 __global__ void __launch_bounds__(kCountThreads) group_count_kernel(const uint4* __restrict__ info, int64_t n,
                                                                     const uint32_t* __restrict__ emit_off, GroupMap gm,
                                                                     int tiles_x, int tiles_y,
@@ -525,11 +525,10 @@ __global__ void __launch_bounds__(kCountThreads) group_count_kernel(const uint4*
     for (int g = threadIdx.x; g < gm.G; g += kCountThreads) hist[g] = 0;
     __syncthreads();
     const int w = threadIdx.x / kWave;
-    constexpr int NW = kCountThreads / kWave;
-    const int64_t first = chunk * kGroupChunk;
+    const int64_t first = chunk * gm.chunk;
     constexpr int R = kExpandRounds;
-    for (int it = 0; it < kGroupChunk / kCountThreads; ++it) {
-        const int64_t g0 = first + (int64_t)(it * NW + w) * kWave;
+    for (int o = w * kWave; o < gm.chunk; o += kCountThreads) {
+        const int64_t g0 = first + o;
         for_wave_entries_at<R, false, false>(g0, info, n, emit_off, tiles_x, tiles_y, nullptr, NearKey{}, gm.K,
                                              &U.c.wg[w], [&](const Ent (&en)[R]) {
 #pragma unroll
@@ -563,7 +562,6 @@ __global__ void __launch_bounds__(kScatterThreads) group_scatter_kernel(const ui
                                                             GroupSplit sp, const int64_t* __restrict__ stop) {
     if (stop && stop[2]) return;
     constexpr int NT = kScatterThreads, NW = NT / kWave;
-    static_assert(kGroupChunk % NT == 0, "whole wavefront slabs per chunk");
     if (sp.list) {
         const int64_t words = (int64_t)sp.ctl[0] * sp.stride;
         for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < words; i += (int64_t)gridDim.x * NT) sp.hist[i] = 0;
@@ -576,10 +574,10 @@ __global__ void __launch_bounds__(kScatterThreads) group_scatter_kernel(const ui
     for (int g = threadIdx.x; g < gm.G; g += NT) cursor[g] = group_off[g] + row[g];
     __syncthreads();
     const int w = threadIdx.x / kWave;
-    const int64_t first = (int64_t)blockIdx.x * kGroupChunk;
+    const int64_t first = (int64_t)blockIdx.x * gm.chunk;
     constexpr int R = kExpandRounds;
-    for (int it = 0; it < kGroupChunk / NT; ++it) {
-        const int64_t g0 = first + (int64_t)(it * NW + w) * kWave;
+    for (int o = w * kWave; o < gm.chunk; o += NT) {
+        const int64_t g0 = first + o;
         for_wave_entries_at<R, true, VAR>(
             g0, info, n, emit_off, tiles_x, tiles_y, zrange, nk, gm.K * gm.SB, &wg[w], [&](const Ent (&en)[R]) {
 #pragma unroll
@@ -1226,7 +1224,7 @@ hipError_t launch_tile_place(const TileOrder& to, hipStream_t s) {
 }
 
 GroupMap group_map(int64_t T, int K, int sub) {
-    GroupMap gm{K, 1, 0, 0, 1, 0, T, nullptr, nullptr, nullptr};
+    GroupMap gm{K, 1, 0, 0, 1, 0, 0, T, nullptr, nullptr, nullptr};
     if (T <= 0 || K <= 0) return gm;
     int64_t gt = K >= kGroupSegTarget ? 1 : kGroupSegTarget / K;
     while ((T + gt - 1) / gt > kMaxGroups) gt *= 2;
@@ -1240,7 +1238,7 @@ GroupMap group_map(int64_t T, int K, int sub) {
 }
 
 GroupMap group_map_var(int64_t T, int K, int sub) {
-    GroupMap gm{K, 1, 0, 0, 1, 0, T, nullptr, nullptr, nullptr};
+    GroupMap gm{K, 1, 0, 0, 1, 0, 0, T, nullptr, nullptr, nullptr};
     if (T <= 0 || K <= 0 || K > kMaxGroupSegs) return gm;
     int64_t gt = std::min<int64_t>(8, kMaxGroupSegs / K);
     while ((T + gt - 1) / gt > kMaxGroups) gt *= 2;
@@ -1255,11 +1253,10 @@ GroupMap group_map_var(int64_t T, int K, int sub) {
 
 hipError_t launch_group_count(const uint32_t* info, int64_t n, const uint32_t* emit_off, GroupMap gm, int tiles_x,
                               int tiles_y, uint32_t* gcount, uint32_t* wgbase, const RangeArgs& ra, hipStream_t s) {
-    static_assert(kGroupChunk % kCountThreads == 0, "whole wavefront slabs per chunk");
     if (ra.samples)
         hipLaunchKernelGGL(range_samples_kernel, dim3((unsigned)((ra.S + 255) / 256)), dim3(256), 0, s,
                            reinterpret_cast<const uint4*>(info), ra.vis_ids, ra.counters, ra.nk, ra.S, ra.samples);
-    const int64_t chunks = (n + kGroupChunk - 1) / kGroupChunk;
+    const int64_t chunks = (n + gm.chunk - 1) / gm.chunk;
     hipLaunchKernelGGL(group_count_kernel, dim3((unsigned)(chunks + 1)), dim3(kCountThreads), 0, s,
                        reinterpret_cast<const uint4*>(info), n, emit_off, gm, tiles_x, tiles_y, gcount, wgbase, ra);
     return hipGetLastError();
@@ -1270,7 +1267,7 @@ hipError_t launch_group_scatter(const uint32_t* info, int64_t n, const uint32_t*
                                 const uint32_t* wgbase, uint64_t* tmp_pair, uint16_t* tmp_code, int64_t capacity,
                                 const GroupSplit& sp, const int64_t* stop, hipStream_t s) {
     if (n == 0) return hipSuccess;
-    const int64_t blocks = (n + kGroupChunk - 1) / kGroupChunk;
+    const int64_t blocks = (n + gm.chunk - 1) / gm.chunk;
     if (gm.seg_base)
         hipLaunchKernelGGL(group_scatter_kernel<true>, dim3((unsigned)blocks), dim3(kScatterThreads), 0, s,
                            reinterpret_cast<const uint4*>(info), n, emit_off, zrange, nk, gm, tiles_x, tiles_y,

@@ -182,7 +182,7 @@ Layout layout(int64_t n, int64_t capacity, int64_t T, int K, int order, bool var
     z += var ? 2 * (size_t)scan_blocks(T) : 0;
     L.status_sel = z;
     z += rules ? 2 * nbb : 0;
-    L.gm = order != TGS_ORDER_BINNED ? GroupMap{K, 1, 0, 0, 1, 0, T, nullptr, nullptr, nullptr}
+    L.gm = order != TGS_ORDER_BINNED ? GroupMap{K, 1, 0, 0, 1, 0, 0, T, nullptr, nullptr, nullptr}
            : var                     ? group_map_var(T, K, sub)
                                      : group_map(T, K, sub);
     const bool grouped = L.gm.G > 0;
@@ -200,7 +200,8 @@ Layout layout(int64_t n, int64_t capacity, int64_t T, int K, int order, bool var
     if (order == TGS_ORDER_BINNED) L.samples = take(sizeof(uint32_t) * 8192);
     L.list_stride = nseg;
     if (grouped) {
-        const size_t chunks = (size_t)((n + kGroupChunk - 1) / kGroupChunk);
+        L.gm.chunk = group_chunk(n);
+        const size_t chunks = (size_t)((n + L.gm.chunk - 1) / L.gm.chunk);
         size_t entry = sizeof(uint32_t);
         if (L.gm.SB > 1) {
             // a queued sub-segment holds two or more of the at most capacity

@@ -115,3 +115,29 @@ def test_expansion(name, order, K):
         first = off[b.seg_base.cpu().numpy()] if order == "per-tile" else off[::K]
     assert np.array_equal(first, np.searchsorted(tiles, np.arange(tx * ty + 1)))
     assert np.array_equal(got, pairs)
+
+
+@pytest.mark.parametrize("n", [255, 256, 257, 65024, 65025, 130048, 130049, 260096, 260097])
+def test_chunks_of_gaussians(n):
+    # around the sizes where a workgroup's share of the Gaussians doubles
+    # (256, 512, 1024, 2048): one tile each, some empty
+    tx, ty = 13, 11
+    rng = np.random.default_rng(n)
+    x, y = rng.integers(0, tx, n), rng.integers(0, ty, n)
+    some = rng.random(n) < 0.9
+    rect = np.stack([x, y, x + some, y + 1], 1)
+    depth = rng.uniform(1.0, 30.0, n).astype(np.float32)
+    ids = np.nonzero(some)[0]
+    tiles = (y * tx + x)[ids]
+    pairs = (depth.view(np.uint32).astype(np.uint64)[ids] << np.uint64(32)) | ids.astype(np.uint64)
+    o = np.lexsort((pairs, tiles))
+    dev = torch.device("cuda:0")
+    cam = scenes.camera(np.eye(3), np.zeros(3), 100.0, 100.0, tx * 8.0, ty * 8.0, tx * 16, ty * 16)
+    s = torch.zeros((n, 16), dtype=torch.float32, device=dev)
+    i = torch.as_tensor(scenes.make_info(depth, rect).view(np.int32)).to(dev)
+    b = tg.Renderer(cam, tg.Params(), device=dev).bin(s, i)
+    torch.cuda.synchronize()
+    assert b.num_entries == len(ids)
+    off = b.offsets.cpu().numpy().view(np.uint32)[::64]
+    assert np.array_equal(off, np.searchsorted(tiles[o], np.arange(tx * ty + 1)))
+    assert np.array_equal(b.pairs[:len(ids)].cpu().numpy().view(np.uint64), pairs[o])
