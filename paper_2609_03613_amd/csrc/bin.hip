@@ -219,23 +219,6 @@ __global__ void __launch_bounds__(kRangeThreads) depth_range_kernel(const uint4*
     depth_range_block(info, vis_ids, counters, nk, S, p_lo, p_hi, pad, znear, zfar, zrange, samples, R);
 }
 
-// Log-depth bin: the clamped log-space map floor(K u), realised with the
-// IEEE-754 bit pattern of the binary32 depth as the logarithm (monotone,
-// piecewise-linear log2), evaluated exactly in integers.
-// K (L - Lmin) < 2^52 (K < 2^20) is exact in binary64, its product with inv = 1 /
-// (Lmax - Lmin) off by one at most, which the exact remainder corrects (the
-// 64-bit integer division takes four times the instructions).
-__device__ __forceinline__ uint32_t bin_of(uint32_t L, uint32_t Lmin, uint32_t Lmax, double inv, int K) {
-    if (Lmax <= Lmin || L <= Lmin) return 0u;
-    if (L >= Lmax) return (uint32_t)(K - 1);
-    const uint32_t d = L - Lmin, r = Lmax - Lmin;
-    uint32_t q = (uint32_t)((double)K * (double)d * inv);
-    const int64_t rem = (int64_t)((uint64_t)K * d - (uint64_t)q * r);
-    if (rem < 0) --q;
-    if (rem >= (int64_t)r) ++q;
-    return min(q, (uint32_t)(K - 1));
-}
-
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -254,7 +237,7 @@ struct WaveGauss {
 
 // Position of depth bits L in the depth range as a 32-bit fraction,
 // floor(2^32 (L - Lmin) / (Lmax - Lmin)), clamped to [0, 2^32 - 1]. For K =
-// 2^k bins, frac >> (32 - k) equals bin_of(L, Lmin, Lmax, K) exactly (floor
+// 2^k bins, frac >> (32 - k) equals the bin (DepthBins) exactly (floor
 // of a floor divided by an integer), which lets each tile pick its own
 // power-of-two bin count from one per-Gaussian value.
 __device__ __forceinline__ uint32_t depth_frac(uint32_t L, uint32_t Lmin, uint32_t Lmax) {
@@ -320,13 +303,8 @@ __device__ __forceinline__ void for_wave_entries_at(int64_t g0, const uint4* __r
     if (total == 0) return;
     const uint32_t excl = incl - (uint32_t)cnt;
     const uint32_t slot = rank_in(ballot(cnt != 0));
-    uint32_t Lmin = 0, Lmax = 0;
-    double inv = 0.0;
-    if (WITH_BIN) {
-        Lmin = __float_as_uint(zrange[0]);
-        Lmax = __float_as_uint(zrange[1]);
-        if (!VAR) inv = 1.0 / (double)(Lmax - Lmin);
-    }
+    DepthBins bins;
+    if (WITH_BIN && !VAR) bins = DepthBins(zrange, K);
     if (cnt) {
         const uint32_t w = (uint32_t)(x1 - x0);
         W->rect[slot] = make_uint4(excl, (uint32_t)x0 | ((uint32_t)y0 << 16), w,
@@ -334,7 +312,7 @@ __device__ __forceinline__ void for_wave_entries_at(int64_t g0, const uint4* __r
         uint32_t bin = 0;
         if (WITH_BIN) {
             const uint32_t bk = nk(key, g);
-            bin = VAR ? depth_frac(bk, Lmin, Lmax) : bin_of(bk, Lmin, Lmax, inv, K);
+            bin = VAR ? depth_frac(bk, __float_as_uint(zrange[0]), __float_as_uint(zrange[1])) : bins(bk);
         }
         W->key[slot] = make_uint4(key, bin, (uint32_t)l, 0u);
     }
@@ -550,7 +528,9 @@ __global__ void __launch_bounds__(kCountThreads) group_count_kernel(const uint4*
 #endif
 constexpr int kScatterThreads = TGS_SCATTER_THREADS;  // threads of a group-scatter workgroup
 
-template <bool VAR>
+// TAG: the entry's tile within the group goes into the spare upper bits of its
+// id, and no code is written (kTagMin).
+template <bool VAR, bool TAG>
 __global__ void __launch_bounds__(kScatterThreads) group_scatter_kernel(const uint4* __restrict__ info, int64_t n,
                                                             const uint32_t* __restrict__ emit_off,
                                                             const float* __restrict__ zrange, NearKey nk, GroupMap gm,
@@ -578,13 +558,20 @@ __global__ void __launch_bounds__(kScatterThreads) group_scatter_kernel(const ui
     constexpr int R = kExpandRounds;
     for (int o = w * kWave; o < gm.chunk; o += NT) {
         const int64_t g0 = first + o;
-        for_wave_entries_at<R, true, VAR>(
+        for_wave_entries_at<R, !TAG, VAR>(
             g0, info, n, emit_off, tiles_x, tiles_y, zrange, nk, gm.K * gm.SB, &wg[w], [&](const Ent (&en)[R]) {
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     if (!en[r].ok) continue;
                     const uint32_t t = tile_id(en[r], tiles_x);
                     const uint32_t grp = group_of(gm, t);
+                    if (TAG) {
+                        const uint32_t pos = atomicAdd(&cursor[grp], 1u);
+                        if (pos >= capacity) continue;
+                        const uint32_t tag = (t - __umul24(grp, (uint32_t)gm.GT)) << (31 - gm.tag_bits) << 1;
+                        tmp_pair[pos] = ((uint64_t)en[r].key << 32) | (tag | (uint32_t)en[r].gid);
+                        continue;
+                    }
                     uint32_t code;
                     if (VAR) {
                         // en.bin is the depth fraction: bin = frac >> shift, then
@@ -1224,7 +1211,7 @@ hipError_t launch_tile_place(const TileOrder& to, hipStream_t s) {
 }
 
 GroupMap group_map(int64_t T, int K, int sub) {
-    GroupMap gm{K, 1, 0, 0, 1, 0, 0, T, nullptr, nullptr, nullptr};
+    GroupMap gm{K, 1, 0, 0, 1, 0, 0, 0, false, T, nullptr, nullptr, nullptr};
     if (T <= 0 || K <= 0) return gm;
     int64_t gt = K >= kGroupSegTarget ? 1 : kGroupSegTarget / K;
     while ((T + gt - 1) / gt > kMaxGroups) gt *= 2;
@@ -1238,7 +1225,7 @@ GroupMap group_map(int64_t T, int K, int sub) {
 }
 
 GroupMap group_map_var(int64_t T, int K, int sub) {
-    GroupMap gm{K, 1, 0, 0, 1, 0, 0, T, nullptr, nullptr, nullptr};
+    GroupMap gm{K, 1, 0, 0, 1, 0, 0, 0, false, T, nullptr, nullptr, nullptr};
     if (T <= 0 || K <= 0 || K > kMaxGroupSegs) return gm;
     int64_t gt = std::min<int64_t>(8, kMaxGroupSegs / K);
     while ((T + gt - 1) / gt > kMaxGroups) gt *= 2;
@@ -1268,14 +1255,12 @@ hipError_t launch_group_scatter(const uint32_t* info, int64_t n, const uint32_t*
                                 const GroupSplit& sp, const int64_t* stop, hipStream_t s) {
     if (n == 0) return hipSuccess;
     const int64_t blocks = (n + gm.chunk - 1) / gm.chunk;
-    if (gm.seg_base)
-        hipLaunchKernelGGL(group_scatter_kernel<true>, dim3((unsigned)blocks), dim3(kScatterThreads), 0, s,
-                           reinterpret_cast<const uint4*>(info), n, emit_off, zrange, nk, gm, tiles_x, tiles_y,
-                           group_off, wgbase, tmp_pair, tmp_code, capacity, sp, stop);
-    else
-        hipLaunchKernelGGL(group_scatter_kernel<false>, dim3((unsigned)blocks), dim3(kScatterThreads), 0, s,
-                           reinterpret_cast<const uint4*>(info), n, emit_off, zrange, nk, gm, tiles_x, tiles_y,
-                           group_off, wgbase, tmp_pair, tmp_code, capacity, sp, stop);
+    const auto kernel = gm.seg_base ? group_scatter_kernel<true, false>
+                        : gm.tagged ? group_scatter_kernel<false, true>
+                                    : group_scatter_kernel<false, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kScatterThreads), 0, s, reinterpret_cast<const uint4*>(info),
+                       n, emit_off, zrange, nk, gm, tiles_x, tiles_y, group_off, wgbase, tmp_pair, tmp_code, capacity,
+                       sp, stop);
     return hipGetLastError();
 }
 

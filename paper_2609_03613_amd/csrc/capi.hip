@@ -182,7 +182,7 @@ Layout layout(int64_t n, int64_t capacity, int64_t T, int K, int order, bool var
     z += var ? 2 * (size_t)scan_blocks(T) : 0;
     L.status_sel = z;
     z += rules ? 2 * nbb : 0;
-    L.gm = order != TGS_ORDER_BINNED ? GroupMap{K, 1, 0, 0, 1, 0, 0, T, nullptr, nullptr, nullptr}
+    L.gm = order != TGS_ORDER_BINNED ? GroupMap{K, 1, 0, 0, 1, 0, 0, 0, false, T, nullptr, nullptr, nullptr}
            : var                     ? group_map_var(T, K, sub)
                                      : group_map(T, K, sub);
     const bool grouped = L.gm.G > 0;
@@ -569,6 +569,10 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
             gm.tile_seg = tile_seg;
             gm.ginfo = (uint4*)(w + L.ginfo);
         }
+        // no codes for many entries, where the tile within the group fits above
+        // the id and the bin follows from the sort key
+        while (1 << gm.tag_bits < gm.GT) ++gm.tag_bits;
+        gm.tagged = cap > kTagMin && !var && !params->near_shift && n <= (int64_t)1 << (32 - gm.tag_bits);
         uint32_t* gcount = zero + L.gcount;
         uint32_t* group_off = (uint32_t*)(w + L.group_off);
         uint32_t* wgbase = (uint32_t*)(w + L.wgbase);
@@ -600,7 +604,7 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
         uint32_t* queued = (uint32_t*)(w + L.queued);
         const bool all = params->repair == TGS_REPAIR_ALL;
         const RepairSum sum{all ? queued : nullptr, gm.G, out->counters_dev};
-        TGS_HIP(launch_group_sort(tmp_pair, tmp_code, group_off, group_order, gm, nseg, cap, out->pairs_dev,
+        TGS_HIP(launch_group_sort(tmp_pair, tmp_code, group_off, group_order, out->zrange_dev, gm, nseg, cap, out->pairs_dev,
                                   out->offsets_dev, seg_lists, L.list_stride, bucket_count, out->counters_dev, all,
                                   out->repaired_dev, rs, queued, tile_count, sp, (uint16_t*)(w + L.part_tile), s),
                 "group sort");

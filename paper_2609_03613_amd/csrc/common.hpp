@@ -73,6 +73,32 @@ __device__ __forceinline__ int rect_of(const uint4& in, int tiles_x, int tiles_y
     return (x1 - x0) * (y1 - y0);
 }
 
+// Log-depth bin: the clamped log-space map floor(K u), realised with the
+// IEEE-754 bit pattern of the binary32 depth as the logarithm (monotone,
+// piecewise-linear log2), exactly floor(K (L - Lmin) / (Lmax - Lmin)) for K <
+// 2^19. The quotient's binary32 estimate with a factor rounded down by 2^-20 is
+// at most the exact one and less than one below it, so the remainder is below
+// 2 (Lmax - Lmin) < 2^32 and decides in 32 bits (a 64-bit integer division takes
+// ten times the instructions).
+struct DepthBins {
+    uint32_t Lmin, Lmax, r;
+    float kr;
+    int K;
+    __device__ __forceinline__ DepthBins() {}
+    __device__ __forceinline__ DepthBins(const float* __restrict__ zrange, int bins) : K(bins) {
+        Lmin = __float_as_uint(zrange[0]);
+        Lmax = __float_as_uint(zrange[1]);
+        r = Lmax > Lmin ? Lmax - Lmin : 1u;
+        kr = (float)K / (float)r * (1.0f - 0x1p-20f);
+    }
+    __device__ __forceinline__ uint32_t operator()(uint32_t L) const {
+        const uint32_t d = max(min(L, Lmax), Lmin) - Lmin;
+        if (r >> 31) return min((uint32_t)((uint64_t)(uint32_t)K * d / r), (uint32_t)(K - 1));
+        const uint32_t q = (uint32_t)((float)d * kr);
+        return min(q + ((uint32_t)K * d - q * r >= r ? 1u : 0u), (uint32_t)(K - 1));
+    }
+};
+
 // XCD (accelerator complex die) executing the calling wave, 0..7.
 __device__ __forceinline__ int xcc_id() {
     return (int)(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & 7u);
@@ -215,6 +241,8 @@ struct GroupMap {
     int K, GT, G, GS, SB;
     uint32_t GT_mul;  // ceil(2^32 / GT), or 0
     int chunk;        // Gaussians per workgroup of the group count and scatter
+    int tag_bits;     // bits of a tile number within the group
+    bool tagged;      // the grouped pairs carry it above the id, and no codes are stored (kTagMin)
     int64_t T;
     const uint32_t* seg_base;
     const uint2* tile_seg;
@@ -230,6 +258,16 @@ constexpr int kSubBins = TGS_SUB_BINS;  // sub-bins per bin in exact-repair mode
 constexpr int kGroupSegTarget = TGS_GROUP_SEGS;  // segments per group aimed at
 constexpr int kMaxGroups = 8192;      // LDS counters of one workgroup
 constexpr int kMaxGroupSegs = 4096;   // LDS counters of one group sort
+// Entries of the capacity from which on the grouped pairs carry their tile
+// instead of a stored code (which then follows from the depth). The scatter's
+// scattered stores bound it, one of 8 and one of 2 bytes per entry: without the
+// second 290 -> 165 us for 10 million Gaussians on 1920x1080, 57 -> 31 for a
+// 1297x840 training step of 500 thousand. The group sort reads 8 bytes instead
+// of 2 to count an entry, which where there are fewer entries costs the longest
+// group more than the scatter gains (a frame of one million on 1920x1080, 4
+// million of capacity: 355.5 us, 357.5 with tiles; the training step, 8.8
+// million: 699, 674 with tiles).
+constexpr int64_t kTagMin = 6 << 20;
 // Gaussians per workgroup of the group count / scatter: 2048, and fewer, down to
 // 256, while that makes fewer than kMinChunks workgroups, each a chain of slabs
 // one after the other (binning 20 thousand Gaussians 62.6 us with 2048, now 57.9;
@@ -434,8 +472,8 @@ hipError_t launch_bin_scatter(const uint32_t* info, int64_t n, const uint32_t* e
 // wgbase [ceil(n / gm.chunk) x G] receives each workgroup's slice base
 // in the groups it touches. group_scan: group_off [G + 1] = exclusive
 // prefix of gcount. group_scatter: tmp_pair / tmp_code [capacity] get every
-// entry (pair, segment within its group) grouped by group; positions past
-// the capacity are dropped; order [G] = the groups, longest first.
+// entry (pair, segment within its group; no codes with gm.tagged) grouped by
+// group; positions past the capacity are dropped; order [G] = the groups, longest first.
 // group_sort: pairs in (tile, bin) order, bin_off
 // [S + 1] (S = T K), repair queues and repaired[] as launch_bin_offsets,
 // single-entry segments' records; bucket_count must be zero. With SB > 1
@@ -459,8 +497,8 @@ hipError_t launch_group_scatter(const uint32_t* info, int64_t n, const uint32_t*
                                 NearKey nk, GroupMap gm, int tiles_x, int tiles_y, const uint32_t* group_off,
                                 const uint32_t* wgbase, uint64_t* tmp_pair, uint16_t* tmp_code, int64_t capacity,
                                 const GroupSplit& sp, const int64_t* stop, hipStream_t s);
-hipError_t launch_group_sort(const uint64_t* tmp_pair, const uint16_t* tmp_code, const uint32_t* group_off,
-                             const uint32_t* order, GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* pairs, uint32_t* bin_off,
+hipError_t launch_group_sort(const uint64_t* tmp_pair, uint16_t* tmp_code, const uint32_t* group_off,
+                             const uint32_t* order, const float* zrange, GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* pairs, uint32_t* bin_off,
                              uint32_t* lists, int64_t list_stride, uint32_t* bucket_count,
                              const int64_t* counters, bool queue_all, uint8_t* repaired, RecordSink rs,
                              uint32_t* queued, uint32_t* tile_count, const GroupSplit& sp, uint16_t* part_tile,

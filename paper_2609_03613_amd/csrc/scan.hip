@@ -793,6 +793,27 @@ __device__ __forceinline__ int64_t first_code(const GroupMap& gm, const GroupCod
     return gm.seg_base ? ((int64_t)gm.seg_base[t] - c.sbase) * c.SB : (t - (int64_t)g * gm.GT) * gm.K * c.SB;
 }
 
+// The grouped pairs with the tile number above the id (GroupMap::tagged): an
+// entry's code and its plain pair.
+template <bool TAG>
+struct GroupedPairs {
+    DepthBins bins;
+    uint32_t id_mask;
+    int shift;
+    __device__ __forceinline__ GroupedPairs(const float* __restrict__ zrange, const GroupMap& gm) {
+        if (!TAG) return;
+        bins = DepthBins(zrange, gm.K * gm.SB);
+        shift = 31 - gm.tag_bits;  // (shifted once more: tag_bits may be 0)
+        id_mask = 0xFFFFFFFFu >> gm.tag_bits;
+    }
+    __device__ __forceinline__ uint32_t code_of(uint64_t p) const {
+        return __umul24((uint32_t)p >> shift >> 1, (uint32_t)bins.K) + bins((uint32_t)(p >> 32));
+    }
+    __device__ __forceinline__ uint64_t plain(uint64_t p) const {
+        return TAG ? (p & ((uint64_t)0xFFFFFFFFu << 32 | id_mask)) : p;
+    }
+};
+
 // Per-group results from pre[] (LDS), the exclusive prefix of the group's n
 // entries over its codes: the bin offsets and repair flags of its segments,
 // the entries of its repaired segments (queued[g]) and of its tiles
@@ -881,9 +902,10 @@ __device__ __forceinline__ uint32_t tile_of_code(const GroupMap& gm, const Group
 // With sp.list, the groups that are split are left out here, and the first
 // sp.slice_grid workgroups count their entries per code, slice by slice, into
 // sp.hist (see group_split_kernel).
+template <bool TAG>
 __global__ void __launch_bounds__(kSortThreads, 4) group_sort_kernel(
-    const uint64_t* __restrict__ tmp_pair, const uint16_t* __restrict__ tmp_code, const uint32_t* __restrict__ group_off,
-    const uint32_t* __restrict__ order, GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* __restrict__ pairs,
+    const uint64_t* __restrict__ tmp_pair, uint16_t* tmp_code, const uint32_t* __restrict__ group_off,
+    const uint32_t* __restrict__ order, const float* __restrict__ zrange, GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* __restrict__ pairs,
     uint32_t* __restrict__ bin_off, uint32_t* __restrict__ lists, int64_t list_stride,
     uint32_t* __restrict__ bucket_count, const int64_t* __restrict__ counters, bool queue_all,
     uint8_t* __restrict__ repaired, RecordSink rs, uint32_t* __restrict__ queued, uint32_t* __restrict__ tile_count,
@@ -897,9 +919,26 @@ __global__ void __launch_bounds__(kSortThreads, 4) group_sort_kernel(
     __shared__ uint16_t scode[kStage];
     __shared__ uint32_t lds32[NT / kWave];
     __shared__ uint32_t lcount[kBuckets], lbase[kBuckets];
-    // adds the codes of entries [lo, hi) to hist
-    auto count = [&](uint32_t lo, uint32_t hi) {
+    const GroupedPairs<TAG> in(zrange, gm);
+    // adds the codes of entries [lo, hi) to hist, and keeps them (for the same
+    // thread) when they had to be worked out and will be needed again
+    auto count = [&](uint32_t lo, uint32_t hi, bool keep) {
         for (uint32_t base = lo; base < hi; base += NT * kSortBatch) {
+            if (TAG) {
+                uint64_t pr[kSortBatch];
+#pragma unroll
+                for (int j = 0; j < kSortBatch; ++j)
+                    pr[j] = tmp_pair[min(base + (uint32_t)(j * NT) + threadIdx.x, hi - 1)];
+#pragma unroll
+                for (int j = 0; j < kSortBatch; ++j) {
+                    const uint32_t e = base + (uint32_t)(j * NT) + threadIdx.x;
+                    if (e >= hi) continue;
+                    const uint32_t c = in.code_of(pr[j]);
+                    atomicAdd(&hist[c], 1u);
+                    if (keep) tmp_code[e] = (uint16_t)c;
+                }
+                continue;
+            }
             uint32_t c[kSortBatch];
 #pragma unroll
             for (int j = 0; j < kSortBatch; ++j) {
@@ -927,7 +966,7 @@ __global__ void __launch_bounds__(kSortThreads, 4) group_sort_kernel(
             const int codes = codes_of(gm, (int)first.x, nseg).codes;
             for (int c = threadIdx.x; c < codes; c += NT) hist[c] = 0;
             __syncthreads();
-            count(first.z, stop);
+            count(first.z, stop, false);
             __syncthreads();
             uint32_t* gh = sp.hist + (int64_t)first.y * sp.stride;
             for (int c = threadIdx.x; c < codes; c += NT)
@@ -962,7 +1001,27 @@ __global__ void __launch_bounds__(kSortThreads, 4) group_sort_kernel(
     __syncthreads();
     const uint32_t n = hi - lo;
     const bool staged = gm.SB > 1 && n <= (uint32_t)kStage;
-    count(lo, hi);
+    // a staged group's entries stay in registers from the count to the placement
+    constexpr int kHeld = kStage / NT;
+    uint32_t held_code[kHeld];
+    uint64_t held_pair[kHeld];
+    auto held = [&](int j) { return (uint32_t)(j * NT) + threadIdx.x < n; };
+    if (staged) {
+#pragma unroll
+        for (int j = 0; j < kHeld; ++j) {
+            const uint32_t e = min(lo + (uint32_t)(j * NT) + threadIdx.x, hi - 1);
+            held_pair[j] = tmp_pair[e];
+            if (!TAG) held_code[j] = tmp_code[e];
+        }
+#pragma unroll
+        for (int j = 0; j < kHeld; ++j) {
+            if (!held(j)) continue;
+            if (TAG) held_code[j] = in.code_of(held_pair[j]);
+            atomicAdd(&hist[held_code[j]], 1u);
+        }
+    } else {
+        count(lo, hi, true);
+    }
     __syncthreads();
     // exclusive prefix of the code counts: thread i owns codes i per ..
     uint32_t ex[kMaxPer], sum = 0;
@@ -1005,26 +1064,12 @@ __global__ void __launch_bounds__(kSortThreads, 4) group_sort_kernel(
     group_results<NT>(gm, gc, g, lo, n, cur, queue, bin_off, repaired, queued, tile_count, lds32);
     if (staged) {
         // place at the code offsets in LDS ...
-        for (uint32_t base = lo; base < hi; base += NT * kSortBatch) {
-            uint32_t c[kSortBatch];
-            uint64_t pr[kSortBatch];
 #pragma unroll
-            for (int j = 0; j < kSortBatch; ++j) {
-                const uint32_t e = base + (uint32_t)(j * NT) + threadIdx.x;
-                c[j] = kNone;
-                pr[j] = 0;
-                if (e < hi) {
-                    c[j] = tmp_code[e];
-                    pr[j] = tmp_pair[e];
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < kSortBatch; ++j) {
-                if (c[j] == kNone) continue;
-                const uint32_t q = atomicAdd(&cur[c[j]], 1u);
-                stage[q] = pr[j];
-                scode[q] = (uint16_t)c[j];
-            }
+        for (int j = 0; j < kHeld; ++j) {
+            if (!held(j)) continue;
+            const uint32_t q = atomicAdd(&cur[held_code[j]], 1u);
+            stage[q] = in.plain(held_pair[j]);
+            scode[q] = (uint16_t)held_code[j];
         }
         __syncthreads();
         // ... and write the group out in order, short sub-segments by rank
@@ -1055,9 +1100,10 @@ __global__ void __launch_bounds__(kSortThreads, 4) group_sort_kernel(
             for (int j = 0; j < kSortBatch; ++j) {
                 if (c[j] == kNone) continue;
                 const uint32_t p = lo + atomicAdd(&cur[c[j]], 1u);
-                pairs[p] = pr[j];
+                const uint64_t v = in.plain(pr[j]);
+                pairs[p] = v;
                 // records exist only with SB == 1, where a code is a segment
-                if (rs.masks && hist[c[j]] == 1u) rs.put((uint32_t)(gc.sbase + c[j]), p, pr[j]);
+                if (rs.masks && hist[c[j]] == 1u) rs.put((uint32_t)(gc.sbase + c[j]), p, v);
             }
         }
     }
@@ -1096,9 +1142,10 @@ struct SplitLds {
 constexpr int kPartBits = 11;
 static_assert(1 << kPartBits == kMaxParts, "part numbers");
 
+template <bool TAG>
 __global__ void __launch_bounds__(kSplitThreads) group_split_kernel(
     const uint64_t* __restrict__ tmp_pair, const uint16_t* __restrict__ tmp_code, const uint32_t* __restrict__ group_off,
-    GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* __restrict__ pairs, uint16_t* __restrict__ part_tile,
+    const float* __restrict__ zrange, GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* __restrict__ pairs, uint16_t* __restrict__ part_tile,
     uint32_t* __restrict__ bin_off, const int64_t* __restrict__ counters, uint8_t* __restrict__ repaired,
     uint32_t* __restrict__ queued, uint32_t* __restrict__ tile_count, GroupSplit sp) {
     constexpr int NT = kSplitThreads;
@@ -1108,6 +1155,7 @@ __global__ void __launch_bounds__(kSplitThreads) group_split_kernel(
     __shared__ SplitLds L;
     __shared__ uint32_t lds32[NT / kWave];
     __shared__ uint32_t unit0;
+    const GroupedPairs<TAG> in(zrange, gm);
     uint4 next = sp.list[blockIdx.x];  // (the grid is at most the list's length)
     const uint32_t slices = sp.ctl[1];
     for (uint32_t it = blockIdx.x; it < slices; it += gridDim.x) {
@@ -1125,8 +1173,8 @@ __global__ void __launch_bounds__(kSplitThreads) group_split_kernel(
 #pragma unroll
         for (int j = 0; j < kEnt; ++j) {
             const uint32_t e = min(sl.z + (uint32_t)(j * NT) + threadIdx.x, sl.w - 1);
-            c[j] = tmp_code[e];
             pr[j] = tmp_pair[e];
+            if (!TAG) c[j] = tmp_code[e];
         }
         uint32_t cnt[kPer], s = 0;
 #pragma unroll
@@ -1183,6 +1231,7 @@ __global__ void __launch_bounds__(kSplitThreads) group_split_kernel(
 #pragma unroll
         for (int j = 0; j < kEnt; ++j) {
             const bool ok = sl.z + (uint32_t)(j * NT) + threadIdx.x < sl.w;
+            if (TAG) c[j] = in.code_of(pr[j]);
             pt[j] = L.part[c[j]] & (kMaxParts - 1);
             rank[j] = ok ? atomicAdd(&L.count[pt[j]], 1u) : 0u;
         }
@@ -1213,7 +1262,7 @@ __global__ void __launch_bounds__(kSplitThreads) group_split_kernel(
         for (int j = 0; j < kEnt; ++j) {
             if (sl.z + (uint32_t)(j * NT) + threadIdx.x >= sl.w) continue;
             const uint32_t i = L.count[pt[j]] + rank[j];
-            L.stage[i] = pr[j];
+            L.stage[i] = in.plain(pr[j]);
             L.code[i] = (uint16_t)c[j];
         }
         __syncthreads();
@@ -1279,18 +1328,18 @@ hipError_t launch_group_scan(const uint32_t* gcount, GroupMap gm, uint32_t* grou
     return hipGetLastError();
 }
 
-hipError_t launch_group_sort(const uint64_t* tmp_pair, const uint16_t* tmp_code, const uint32_t* group_off,
-                             const uint32_t* order, GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* pairs, uint32_t* bin_off,
+hipError_t launch_group_sort(const uint64_t* tmp_pair, uint16_t* tmp_code, const uint32_t* group_off,
+                             const uint32_t* order, const float* zrange, GroupMap gm, int64_t nseg, int64_t capacity, uint64_t* pairs, uint32_t* bin_off,
                              uint32_t* lists, int64_t list_stride, uint32_t* bucket_count,
                              const int64_t* counters, bool queue_all, uint8_t* repaired, RecordSink rs,
                              uint32_t* queued, uint32_t* tile_count, const GroupSplit& sp, uint16_t* part_tile,
                              hipStream_t s) {
-    hipLaunchKernelGGL(group_sort_kernel, dim3((unsigned)(sp.slice_grid + gm.G)), dim3(kSortThreads), 0, s, tmp_pair,
-                       tmp_code, group_off, order, gm, nseg, capacity, pairs, bin_off, lists, list_stride, bucket_count,
+    hipLaunchKernelGGL(gm.tagged ? group_sort_kernel<true> : group_sort_kernel<false>, dim3((unsigned)(sp.slice_grid + gm.G)), dim3(kSortThreads), 0, s, tmp_pair,
+                       tmp_code, group_off, order, zrange, gm, nseg, capacity, pairs, bin_off, lists, list_stride, bucket_count,
                        counters, queue_all, repaired, rs, queued, tile_count, sp);
     if (sp.list) {
-        hipLaunchKernelGGL(group_split_kernel, dim3((unsigned)std::min(sp.max_slices, kSplitGrid)),
-                           dim3(kSplitThreads), 0, s, tmp_pair, tmp_code, group_off, gm, nseg, capacity, pairs,
+        hipLaunchKernelGGL(gm.tagged ? group_split_kernel<true> : group_split_kernel<false>, dim3((unsigned)std::min(sp.max_slices, kSplitGrid)),
+                           dim3(kSplitThreads), 0, s, tmp_pair, tmp_code, group_off, zrange, gm, nseg, capacity, pairs,
                            part_tile, bin_off, counters, repaired, queued, tile_count, sp);
     }
     return hipGetLastError();

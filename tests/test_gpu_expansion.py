@@ -70,6 +70,8 @@ def mixed(tx, ty, n, seed):
     return [tuple(int(v) for v in q) for q in r]
 
 
+TAGGED = (6 << 20) + 1
+
 CASES = {
     "widths 113x9": (113, 9, 16, lambda tx, ty: widths(tx, ty)),
     "counts 32x40": (32, 40, 16, lambda tx, ty: counts(tx, ty)),
@@ -82,7 +84,8 @@ CASES = {
 
 @pytest.mark.parametrize("name", list(CASES))
 @pytest.mark.parametrize("order, K", [("binned", 1), ("binned", 3), ("binned", 64), ("binned", 600), ("binned", 1000),
-                                      ("global", 1), ("per-tile", 4)])
+                                      ("global", 1), ("per-tile", 4), ("tagged", 1), ("tagged", 3), ("tagged", 64),
+                                      ("tagged", 600), ("tagged", 1000)])
 def test_expansion(name, order, K):
     tx, ty, ts, make = CASES[name]
     if tx * ty > 1 << 20 and K > 64:
@@ -100,7 +103,8 @@ def test_expansion(name, order, K):
     r = tg.Renderer(cam, tg.Params(tile_size=ts, num_bins=K, per_tile_bins=kt), device=dev)
     s = torch.zeros((n, 16), dtype=torch.float32, device=dev)
     i = torch.as_tensor(scenes.make_info(depth, rect).view(np.int32)).to(dev)
-    b = r.bin(s, i, "global" if order == "global" else "binned")
+    # "tagged": a capacity from which on the entries carry their tile instead of a code
+    b = r.bin(s, i, "global" if order == "global" else "binned", capacity=TAGGED if order == "tagged" else None)
     torch.cuda.synchronize()
     M = len(pairs)
     assert b.num_entries == M

@@ -74,14 +74,16 @@ CASES = [
 ]
 
 
+# the second capacity: from there on the entries carry their tile instead of a code
+@pytest.mark.parametrize("capacity", [None, (6 << 20) + 1])
 @pytest.mark.parametrize("case", range(len(CASES)))
-def test_split_groups_bit_exact(case):
+def test_split_groups_bit_exact(case, capacity):
     n, W, clusters, tiles = CASES[case]
     depth, rect = scene(n, W, clusters, case, tiles)
     tx = (W + 15) // 16
     for K, sub in ((64, 0), (64, 2), (24, 0)):
         ref = oracle.schedule(depth, rect, tx, 1, K=K, znear=0.01, zfar=1e10)
-        b = bin_of(depth, rect, W, tg.Params(num_bins=K, sub_bins=sub))
+        b = bin_of(depth, rect, W, tg.Params(num_bins=K, sub_bins=sub), capacity=capacity)
         assert b.num_entries == n == ref["M"]
         off = to_np(b.offsets).view(np.uint32)
         assert np.array_equal(off, ref["bin_offsets"]), (K, sub)
