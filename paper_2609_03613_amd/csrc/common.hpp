@@ -293,16 +293,16 @@ GroupMap group_map_var(int64_t T, int K, int sub);
 // entries is split over the chip, by slices of kSlice entries that are ordered
 // by part first; a part is a run of codes with at most 2 kPartLen entries, or
 // one code. One workgroup per group took as long as its longest group: 112 us
-// of group sort on 640x360 with one million Gaussians (now 40 and 45 for the
-// parts), 398 us on 1920x1080 with 10 million (now 60 and 350), with 250 us in
-// the sort of the longest sub-segment behind it (now 37). The line at 16384
-// entries: a split group is read and written once more, which pays where the
-// group sort's scattered stores and the queued sub-segments cost more than that
-// (binning of 10 million Gaussians 1048 us, 1060 at 8192 and 1072 at 32768; a
-// 1297x840 training step 743, 765 and 755). kSplitMean: below 4096 entries of
-// capacity per group, groups that long are rare, and the extra launch and the
-// larger one that mostly find nothing cost 10 us (the frame of one million on
-// 1920x1080, 3922 per group: 397 us against 389).
+// of group sort on 640x360 with one million Gaussians (now 23, and 20 for the
+// split), 398 us on 1920x1080 with 10 million (now 87 and 143), with 249 us for
+// the longest sub-segment behind it (now 36). The line at 16384 entries: a split
+// group is read and written once more, which pays where the group sort's
+// scattered stores and the queued sub-segments cost more than that (binning of
+// 10 million Gaussians 1050 us, 1060 at 8192 and 1072 at 32768; a 1297x840
+// training step 743, 765 and 755). kSplitMean: below 4096 entries of capacity
+// per group, groups that long are rare, and the extra launch and the larger one
+// that mostly find nothing cost 10 us (the frame of one million on 1920x1080,
+// 3922 per group: 397 us against 389).
 constexpr int kSlice = 4096;       // entries per slice workgroup
 constexpr int kPartLen = 2048;     // entries between part boundaries
 constexpr int kMaxParts = 2048;    // LDS counters of one slice workgroup
