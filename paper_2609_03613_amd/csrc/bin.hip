@@ -693,7 +693,7 @@ __device__ __forceinline__ void sort_small(const SmallSort& S, const uint32_t (&
 // are in flight while one is written out.
 constexpr int kPartThreads = 1024;
 constexpr int kPartGrid = 512;          // two workgroups per CU: all its wavefronts
-constexpr int kPartCap = 2 * kPartLen;  // keys of the bucket sort
+constexpr int kPartCap = kPartStep + kPartCode;  // keys of the bucket sort
 using PartLds = BucketLds<kPartThreads, kPartCap>;
 __device__ __forceinline__ void sort_parts(uint64_t* __restrict__ pairs, const uint16_t* __restrict__ part_tile,
                                            uint2* __restrict__ lists, int64_t list_stride,

@@ -227,7 +227,7 @@ Layout layout(int64_t n, int64_t capacity, int64_t T, int K, int order, bool var
             GroupSplit& sp = L.sp;
             sp.max_groups = (int)std::min<int64_t>(L.gm.G, capacity / (kSplitMin + 1) + 1);
             sp.max_slices = (int)(capacity / kSlice) + sp.max_groups;
-            sp.max_units = (int)(3 * capacity / kPartLen) + sp.max_groups;
+            sp.max_units = (int)(capacity / kPartStep + 2 * capacity / kPartCode) + sp.max_groups;
             // the slices are counted beside the groups that are not split; with
             // 512 workgroups for them, where there are few, a 1297x840 training
             // step took 770 us instead of 753

@@ -291,8 +291,10 @@ GroupMap group_map_var(int64_t T, int K, int sub);
 
 // Long groups (exact repair with sub-bins): a group of more than kSplitMin
 // entries is split over the chip, by slices of kSlice entries that are ordered
-// by part first; a part is a run of codes with at most 2 kPartLen entries, or
-// one code. One workgroup per group took as long as its longest group: 112 us
+// by part first; a part is a run of codes with less than kPartStep + kPartCode
+// entries, or one code (3072 and 1024 rather than 2048 and 2048: the parts are
+// fuller, the captured batch of 16 views 9870 us instead of 10407, binning 10
+// million Gaussians 893 instead of 912; 3328 and 768: 9775 and 893). One workgroup per group took as long as its longest group: 112 us
 // of group sort on 640x360 with one million Gaussians (now 23, and 20 for the
 // split), 398 us on 1920x1080 with 10 million (now 87 and 143), with 249 us for
 // the longest sub-segment behind it (now 36). The line at 16384 entries: a split
@@ -304,13 +306,15 @@ GroupMap group_map_var(int64_t T, int K, int sub);
 // that mostly find nothing cost 10 us (the frame of one million on 1920x1080,
 // 3922 per group: 397 us against 389).
 constexpr int kSlice = 4096;       // entries per slice workgroup
-constexpr int kPartLen = 2048;     // entries between part boundaries
+constexpr int kPartStep = 3072;    // entries between part boundaries
+constexpr int kPartCode = 1024;    // a code of more entries is a part by itself
 constexpr int kMaxParts = 2048;    // LDS counters of one slice workgroup
 constexpr uint32_t kSplitMin = 16384;
 constexpr int64_t kSplitMean = 4096;
-// n / kPartLen stretches and two boundaries per code of more than kPartLen
-// entries: at most 3 n / kPartLen + 1 parts. Longer groups are sorted whole.
-constexpr uint32_t kSplitMax = (uint32_t)(kMaxParts - 1) / 3 * kPartLen;
+// n / kPartStep stretches and two boundaries per code of more than kPartCode
+// entries: at most n / kPartStep + 2 n / kPartCode + 1 parts. Longer groups are
+// sorted whole.
+constexpr uint32_t kSplitMax = (uint32_t)((int64_t)(kMaxParts - 1) * kPartStep * kPartCode / (kPartCode + 2 * kPartStep));
 __host__ __device__ __forceinline__ bool split_group(uint32_t n) { return n > kSplitMin && n <= kSplitMax; }
 struct GroupSplit {
     uint4* list;      // slices {group, split index, begin, end}; null: no split groups

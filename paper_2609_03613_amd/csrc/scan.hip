@@ -850,10 +850,10 @@ __device__ __forceinline__ void group_results(const GroupMap& gm, const GroupCod
 }
 
 // Parts of a long group. Its codes are cut into parts that fit the stage:
-// every kPartLen entries (at the next code), and around any code of more than
-// kPartLen entries, which is a part by itself; so every other part has less
-// than 2 kPartLen = kStage entries.
-static_assert(2 * kPartLen == kStage, "parts fit the stage");
+// every kPartStep entries (at the next code), and around any code of more than
+// kPartCode entries, which is a part by itself; so every other part has less
+// than kPartStep + kPartCode = kStage entries.
+static_assert(kPartStep + kPartCode == kStage, "parts fit the stage");
 
 // Thread t holds the counts cnt[] of codes t PER .. and run, the entries
 // before them; prev is the count of the code before. flag[j] = a part starts
@@ -867,7 +867,7 @@ __device__ __forceinline__ uint32_t part_starts(const uint32_t (&cnt)[PER], uint
         const int k = (int)threadIdx.x * PER + j;
         const uint32_t len = cnt[j];
         flag[j] = k > 0 && k < codes &&
-                          (run / kPartLen != (run - prev) / kPartLen || len > kPartLen || prev > kPartLen)
+                          (run / kPartStep != (run - prev) / kPartStep || len > kPartCode || prev > kPartCode)
                       ? 1u
                       : 0u;
         flags += flag[j];

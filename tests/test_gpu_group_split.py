@@ -19,7 +19,8 @@ pytestmark = pytest.mark.gpu
 
 tg = pytest.importorskip("paper_2609_03613_amd")
 
-SPLIT_MAX = 682 * 2048  # the longest group that is split
+SPLIT_MAX = 682 * 2048  # past the longest group that is split
+SPLIT_MOST = 2047 * 3072 * 1024 // (1024 + 2 * 3072)  # that group
 
 
 def to_np(t):
@@ -71,6 +72,10 @@ CASES = [
     (60000, 300, ((20000, 2, 6.0, 0.01), (20000, 15, 9.0, 0.01)), None),  # three groups, the last of 3 tiles
     (SPLIT_MAX, 128, (), None),
     (SPLIT_MAX + 1, 128, (), None),
+    # around a code that is a part by itself (1024 entries) and the boundaries every 3072
+    (20480, 128, ((1024, 1, 5.0, 0.0), (1025, 2, 5.0, 0.0), (3072, 3, 5.0, 0.0), (3073, 4, 6.0, 0.0)), None),
+    (SPLIT_MOST, 128, (), None),
+    (SPLIT_MOST + 1, 128, (), None),
 ]
 
 
