@@ -308,14 +308,13 @@ GroupMap group_map_var(int64_t T, int K, int sub);
 constexpr int kSlice = 4096;       // entries per slice workgroup
 constexpr int kPartStep = 3072;    // entries between part boundaries
 constexpr int kPartCode = 1024;    // a code of more entries is a part by itself
-constexpr int kMaxParts = 2048;    // LDS counters of one slice workgroup
+// LDS counters of a slice workgroup, enough for a part per code: no group is too
+// long (5 million Gaussians on 280x207, three groups of 1.4 million entries, with
+// room for 2048 parts, hence groups of at most 0.9 million: 1980 us, now 795)
+constexpr int kMaxParts = kMaxGroupSegs;
 constexpr uint32_t kSplitMin = 16384;
 constexpr int64_t kSplitMean = 4096;
-// n / kPartStep stretches and two boundaries per code of more than kPartCode
-// entries: at most n / kPartStep + 2 n / kPartCode + 1 parts. Longer groups are
-// sorted whole.
-constexpr uint32_t kSplitMax = (uint32_t)((int64_t)(kMaxParts - 1) * kPartStep * kPartCode / (kPartCode + 2 * kPartStep));
-__host__ __device__ __forceinline__ bool split_group(uint32_t n) { return n > kSplitMin && n <= kSplitMax; }
+__host__ __device__ __forceinline__ bool split_group(uint32_t n) { return n > kSplitMin; }
 struct GroupSplit {
     uint4* list;      // slices {group, split index, begin, end}; null: no split groups
     uint4* units;     // parts of the split groups {begin, length, first tile of the group, tiles}

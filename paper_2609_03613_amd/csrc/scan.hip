@@ -1129,17 +1129,20 @@ constexpr int kSplitGrid = 512;  // two workgroups per CU (LDS)
 struct SplitLds {
     union {
         uint64_t stage[kSlice];
-        uint32_t pre[kMaxGroupSegs];  // exclusive prefix of the code counts (before the staging)
+        struct {  // before the staging
+            uint32_t pre[kMaxGroupSegs];   // exclusive prefix of the code counts
+            uint32_t part[kMaxGroupSegs];  // part | tile of the group << kPartBits of each code
+        };
     };
-    uint16_t code[kSlice];
-    uint32_t part[kMaxGroupSegs];  // part | tile of the group << kPartBits of each code
-    uint32_t begin[kMaxParts];     // first entry of the part, relative to the group; then its place for this slice
+    uint32_t meta[kSlice];      // that of each slot
+    uint32_t begin[kMaxParts];  // first entry of the part, relative to the group; then its place for this slice
     union {
-        uint32_t count[kMaxParts];      // first code; then the slice's entries per part and their exclusive prefix
-        uint32_t tail[kSplitThreads];   // each thread's last code count
+        uint16_t count[kMaxParts];       // first code; then the slice's entries per part and their exclusive prefix
+        uint32_t count2[kMaxParts / 2];  // (two parts to a word, for the additions)
+        uint32_t tail[kSplitThreads];    // each thread's last code count
     };
 };
-constexpr int kPartBits = 11;
+constexpr int kPartBits = 12;
 static_assert(1 << kPartBits == kMaxParts, "part numbers");
 
 template <bool TAG>
@@ -1151,7 +1154,7 @@ __global__ void __launch_bounds__(kSplitThreads) group_split_kernel(
     constexpr int NT = kSplitThreads;
     constexpr int kPer = kMaxGroupSegs / NT;  // codes per thread
     constexpr int kEnt = kSlice / NT;         // entries per thread
-    constexpr int kPpt = kMaxParts / NT;      // parts per thread
+    constexpr int kPpt = kMaxParts / NT;      // parts per thread, at most
     __shared__ SplitLds L;
     __shared__ uint32_t lds32[NT / kWave];
     __shared__ uint32_t unit0;
@@ -1198,7 +1201,7 @@ __global__ void __launch_bounds__(kSplitThreads) group_split_kernel(
         const uint32_t flags = part_starts(cnt, before, threadIdx.x ? L.tail[threadIdx.x - 1] : 0u, gc.codes, flag);
         uint32_t nflags;
         uint32_t p = block_excl_u32<NT>(flags, lds32, &nflags);
-        const uint32_t parts = nflags + 1;  // <= kMaxParts, see split_group
+        const uint32_t parts = nflags + 1;  // at most one per code
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int k = (int)threadIdx.x * kPer + j;
@@ -1207,7 +1210,7 @@ __global__ void __launch_bounds__(kSplitThreads) group_split_kernel(
                 L.part[k] = p | tile_of_code(gm, gc, g, (uint32_t)k) << kPartBits;
                 if (flag[j] || k == 0) {
                     L.begin[p] = L.pre[k];
-                    L.count[p] = (uint32_t)k;  // first code, for the unit list
+                    L.count[p] = (uint16_t)k;  // first code, for the unit list
                 }
             }
         }
@@ -1225,34 +1228,37 @@ __global__ void __launch_bounds__(kSplitThreads) group_split_kernel(
             }
             __syncthreads();
         }
-        for (uint32_t q = threadIdx.x; q < parts; q += NT) L.count[q] = 0;
+        for (uint32_t q = threadIdx.x; q < (parts + 1) / 2; q += NT) L.count2[q] = 0;
         __syncthreads();
-        uint32_t rank[kEnt], pt[kEnt];
+        uint32_t rank[kEnt], mt[kEnt];
 #pragma unroll
         for (int j = 0; j < kEnt; ++j) {
             const bool ok = sl.z + (uint32_t)(j * NT) + threadIdx.x < sl.w;
             if (TAG) c[j] = in.code_of(pr[j]);
-            pt[j] = L.part[c[j]] & (kMaxParts - 1);
-            rank[j] = ok ? atomicAdd(&L.count[pt[j]], 1u) : 0u;
+            mt[j] = L.part[c[j]];
+            const uint32_t q = mt[j] & (kMaxParts - 1), sh = (q & 1u) * 16u;
+            rank[j] = ok ? (atomicAdd(&L.count2[q / 2], 1u << sh) >> sh) & 0xFFFFu : 0u;
         }
         __syncthreads();
         // exclusive prefix over the parts, and each part's place in the output
+        const uint32_t pp = (parts + NT - 1) / NT;  // consecutive parts per thread
         uint32_t pc[kPpt], ps = 0;
 #pragma unroll
-        for (int j = 0; j < kPpt; ++j) {
-            const uint32_t q = threadIdx.x * kPpt + j;
-            pc[j] = q < parts ? L.count[q] : 0u;
+        for (uint32_t j = 0; j < (uint32_t)kPpt; ++j) {
+            const uint32_t q = threadIdx.x * pp + j;
+            pc[j] = j < pp && q < parts ? L.count[q] : 0u;
             ps += pc[j];
         }
         uint32_t base[kPpt];
 #pragma unroll
-        for (int j = 0; j < kPpt; ++j) base[j] = pc[j] ? atomicAdd(&cursor[threadIdx.x * kPpt + j], pc[j]) : 0u;
+        for (uint32_t j = 0; j < (uint32_t)kPpt; ++j)
+            base[j] = pc[j] ? atomicAdd(&cursor[threadIdx.x * pp + j], pc[j]) : 0u;
         uint32_t pex = block_excl_u32<NT>(ps, lds32, &total);
 #pragma unroll
-        for (int j = 0; j < kPpt; ++j) {
-            const uint32_t q = threadIdx.x * kPpt + j;
-            if (q < parts) {
-                L.count[q] = pex;
+        for (uint32_t j = 0; j < (uint32_t)kPpt; ++j) {
+            const uint32_t q = threadIdx.x * pp + j;
+            if (j < pp && q < parts) {
+                L.count[q] = (uint16_t)pex;
                 L.begin[q] += base[j] - pex;  // slot i of the slice goes to begin + i
             }
             pex += pc[j];
@@ -1261,14 +1267,14 @@ __global__ void __launch_bounds__(kSplitThreads) group_split_kernel(
 #pragma unroll
         for (int j = 0; j < kEnt; ++j) {
             if (sl.z + (uint32_t)(j * NT) + threadIdx.x >= sl.w) continue;
-            const uint32_t i = L.count[pt[j]] + rank[j];
+            const uint32_t i = L.count[mt[j] & (kMaxParts - 1)] + rank[j];
             L.stage[i] = in.plain(pr[j]);
-            L.code[i] = (uint16_t)c[j];
+            L.meta[i] = mt[j];
         }
         __syncthreads();
         const uint32_t m = sl.w - sl.z;
         for (uint32_t i = threadIdx.x; i < m; i += NT) {
-            const uint32_t k = L.part[L.code[i]];
+            const uint32_t k = L.meta[i];
             const uint32_t to = lo + L.begin[k & (kMaxParts - 1)] + i;
             pairs[to] = L.stage[i];
             part_tile[to] = (uint16_t)(k >> kPartBits);

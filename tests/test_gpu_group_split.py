@@ -5,8 +5,8 @@ bit-exact against the oracle's schedule at the edges: just above the group
 sort's stage (4096), the longest group that is not split and one entry more,
 whole and ragged slices, a sub-segment that is a part by itself (more than 2048
 entries) up to and past the workgroup sort (8192), buckets of 512 and 513 equal
-depths, narrow depth clusters inside one sub-bin, the longest group that is
-split and one entry more, several groups, per-tile bin counts, the capacity from
+depths, narrow depth clusters inside one sub-bin, groups of a million and a half
+entries (one part per thread and more), several groups, per-tile bin counts, the capacity from
 which on groups are split, and a truncated stream."""
 import numpy as np
 import pytest
@@ -19,8 +19,8 @@ pytestmark = pytest.mark.gpu
 
 tg = pytest.importorskip("paper_2609_03613_amd")
 
-SPLIT_MAX = 682 * 2048  # past the longest group that is split
-SPLIT_MOST = 2047 * 3072 * 1024 // (1024 + 2 * 3072)  # that group
+SPLIT_MAX = 682 * 2048  # more parts than one per 512 threads and, below, about that many
+SPLIT_MOST = 512 * 3072
 
 
 def to_np(t):
