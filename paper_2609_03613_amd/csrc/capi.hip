@@ -360,6 +360,18 @@ struct CountSlot {
     hipEvent_t written = nullptr;
     int device = -1;
 };
+// Another thread may be capturing in the global mode, under which an allocation
+// here would be refused and end its capture; nothing here is part of one.
+class RelaxedCapture {
+  public:
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+    RelaxedCapture(const RelaxedCapture&) = delete;
+    RelaxedCapture& operator=(const RelaxedCapture&) = delete;
+
+  private:
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+};
 class CountSlots {
   public:
     hipError_t take(CountSlot& out) {
@@ -375,6 +387,7 @@ class CountSlots {
                     return hipSuccess;
                 }
         }
+        const RelaxedCapture relaxed;
         CountSlot s;
         s.device = device;
         e = hipHostMalloc((void**)&s.host, sizeof(int64_t), hipHostMallocPortable | hipHostMallocMapped);
@@ -399,6 +412,7 @@ class CountSlots {
 
   private:
     static void release(const CountSlot& s) {
+        const RelaxedCapture relaxed;
         if (s.written) (void)hipEventDestroy(s.written);
         if (s.host) (void)hipHostFree(s.host);
     }

@@ -145,3 +145,45 @@ def test_chunks_of_gaussians(n):
     off = b.offsets.cpu().numpy().view(np.uint32)[::64]
     assert np.array_equal(off, np.searchsorted(tiles[o], np.arange(tx * ty + 1)))
     assert np.array_equal(b.pairs[:len(ids)].cpu().numpy().view(np.uint64), pairs[o])
+
+
+@pytest.mark.parametrize("mode", [dict(packed=1), dict(packed=2), dict(repair="rules"), dict(repair="none"), dict(sub_bins=1),
+                                  dict(sub_bins=2, num_bins=100), dict(tile_size=8, num_bins=7),
+                                  dict(tile_size=32, num_bins=1024), dict(near_shift=1)])
+def test_modes_with_and_without_codes(mode):
+    # the two forms of the grouped entries under every mode that reaches them:
+    # the same segments (in pair order where they are sorted), records, masks
+    W, H, n = 400, 300, 6000
+    splats, info = scenes.random_splats(n, W, H, seed=11)
+    if "tile_size" in mode:
+        rect = scenes.info_rects(info) * 16
+        ts = mode["tile_size"]
+        rect = np.stack([rect[:, 0] // ts, rect[:, 1] // ts, -(-rect[:, 2] // ts), -(-rect[:, 3] // ts)], 1)
+        info = scenes.make_info(info[:, 0].view(np.float32), rect)
+    cam = scenes.camera(np.eye(3), np.zeros(3), 100.0, 100.0, W / 2, H / 2, W, H)
+    dev = torch.device("cuda:0")
+    s = torch.as_tensor(splats).to(dev)
+    i = torch.as_tensor(info.view(np.int32)).to(dev)
+    got = []
+    for capacity in (None, TAGGED):
+        r = tg.Renderer(cam, tg.Params(**mode), device=dev)
+        b = r.bin(s, i, "binned", capacity=capacity)
+        torch.cuda.synchronize()
+        M = b.num_entries
+        off = b.offsets.cpu().numpy().view(np.uint32).astype(np.int64)
+        pairs = b.pairs[:M].cpu().numpy().view(np.uint64)
+        seg = np.repeat(np.arange(len(off) - 1), np.diff(off))
+        o = np.lexsort((pairs, seg))
+        rep = b.repaired.cpu().numpy()[:len(off) - 1]
+        out = [off, pairs[o], rep, b.counters.cpu().numpy(), b.zrange.cpu().numpy()]
+        in_order = np.concatenate([[True], (seg[1:] != seg[:-1]) | (pairs[1:] > pairs[:-1])])
+        if "repair" not in mode:
+            assert in_order.all()
+            for k in ("records", "masks"):
+                v = getattr(b, k, None)
+                if v is not None:
+                    out.append(v.cpu().numpy()[:M].view(np.uint8))
+        got.append(out)
+    assert len(got[0]) == len(got[1])
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
