@@ -203,10 +203,16 @@ Layout layout(int64_t n, int64_t capacity, int64_t T, int K, int order, bool var
         L.gm.chunk = group_chunk(n);
         const size_t chunks = (size_t)((n + L.gm.chunk - 1) / L.gm.chunk);
         size_t entry = sizeof(uint32_t);
+        // groups are split with sub-bins (exact repair without records), when
+        // the capacity allows groups that long
+        const bool split = L.gm.SB > 1 && capacity > (int64_t)kSplitMin && capacity > L.gm.G * kSplitMean;
         if (L.gm.SB > 1) {
-            // a queued sub-segment holds two or more of the at most capacity
-            // entries; it is queued as {begin, length}
-            L.list_stride = std::min<int64_t>(nseg * L.gm.SB, capacity / 2 + 1);
+            // queued as {begin, length}, disjoint runs of two or more of the at
+            // most capacity entries: sub-segments, each once, and in the parts of
+            // split groups also buckets of more than kBucketRank entries, several
+            // of which can come from one sub-segment
+            const int64_t buckets = split ? capacity / (kBucketRank + 1) : 0;
+            L.list_stride = std::min<int64_t>(nseg * L.gm.SB + buckets, capacity / 2 + 1);
             entry = sizeof(uint2);
         }
         L.seg_lists = take(entry * (size_t)kBuckets * (size_t)L.list_stride);
@@ -221,9 +227,7 @@ Layout layout(int64_t n, int64_t capacity, int64_t T, int K, int order, bool var
             L.tile_seg = take(sizeof(uint2) * (size_t)T);
             L.ginfo = take(sizeof(uint4) * (size_t)L.gm.G);
         }
-        // groups are split with sub-bins (exact repair without records), when
-        // the capacity allows groups that long
-        if (L.gm.SB > 1 && capacity > (int64_t)kSplitMin && capacity > L.gm.G * kSplitMean) {
+        if (split) {
             GroupSplit& sp = L.sp;
             sp.max_groups = (int)std::min<int64_t>(L.gm.G, capacity / (kSplitMin + 1) + 1);
             sp.max_slices = (int)(capacity / kSlice) + sp.max_groups;

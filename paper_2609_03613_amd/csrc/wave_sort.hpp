@@ -171,7 +171,6 @@ __device__ __forceinline__ void sort_block_reg(uint64_t (&v)[E], uint64_t* lds) 
 // bucket holds one or two keys, so this is one LDS atomic, one LDS write and a
 // few LDS reads per key against the O(log^2) exchanges of the networks.
 constexpr int kBucketSlots = 4096;
-constexpr int kBucketRank = 512;  // longest bucket ordered by rank
 
 template <int NT, int CAP>
 struct BucketLds {
