@@ -297,7 +297,9 @@ TGS_API size_t tgs_bin_workspace_size(int64_t n, int64_t capacity, const tgs_cam
                               const tgs_params* params, int32_t order);
 
 /* Builds the entry stream of `order`. num_entries_host: NULL = no host
-   synchronisation (an overflow is only reported through counters[2]);
+   synchronisation (an overflow is only reported through counters[2]; the
+   stream is then truncated, and empty where the count needs more than 32
+   bits and the binning is grouped);
    non-NULL = wait for the entry count, store it there, and return
    TGS_ERR_CAPACITY without building the stream when it exceeds capacity
    (nothing uses the outputs any more then). Otherwise the rest of the BINNED

@@ -608,7 +608,7 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
             sp.hist = (uint32_t*)(w + L.split_hist);
             sp.ctl = zero + kSplitCtl;
         }
-        TGS_HIP(launch_group_scan(gcount, gm, group_off, group_order, cap, sp, s), "group scan");
+        TGS_HIP(launch_group_scan(gcount, gm, out->counters_dev, group_off, group_order, cap, sp, s), "group scan");
         TGS_HIP(launch_group_scatter(pr->info_dev, n, emit_off, out->zrange_dev, nk, gm, tiles_x, tiles_y, group_off,
                                      wgbase, tmp_pair, tmp_code, cap, sp, stop, s),
                 "group scatter");

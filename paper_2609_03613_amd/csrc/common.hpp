@@ -477,7 +477,8 @@ hipError_t launch_bin_scatter(const uint32_t* info, int64_t n, const uint32_t* e
 // Grouped binning, see GroupMap. group_count: gcount [G] must be zero;
 // wgbase [ceil(n / gm.chunk) x G] receives each workgroup's slice base
 // in the groups it touches. group_scan: group_off [G + 1] = exclusive
-// prefix of gcount. group_scatter: tmp_pair / tmp_code [capacity] get every
+// prefix of gcount (all zero when the entry count counters[0] does not fit 32
+// bits). group_scatter: tmp_pair / tmp_code [capacity] get every
 // entry (pair, segment within its group; no codes with gm.tagged) grouped by
 // group; positions past the capacity are dropped; order [G] = the groups, longest first.
 // group_sort: pairs in (tile, bin) order, bin_off
@@ -497,8 +498,8 @@ hipError_t launch_bin_scatter(const uint32_t* info, int64_t n, const uint32_t* e
 // range (ra) meanwhile, which the group scatter then uses.
 hipError_t launch_group_count(const uint32_t* info, int64_t n, const uint32_t* emit_off, GroupMap gm, int tiles_x,
                               int tiles_y, uint32_t* gcount, uint32_t* wgbase, const RangeArgs& ra, hipStream_t s);
-hipError_t launch_group_scan(const uint32_t* gcount, GroupMap gm, uint32_t* group_off, uint32_t* order,
-                             int64_t capacity, const GroupSplit& sp, hipStream_t s);
+hipError_t launch_group_scan(const uint32_t* gcount, GroupMap gm, const int64_t* counters, uint32_t* group_off,
+                             uint32_t* order, int64_t capacity, const GroupSplit& sp, hipStream_t s);
 hipError_t launch_group_scatter(const uint32_t* info, int64_t n, const uint32_t* emit_off, const float* zrange,
                                 NearKey nk, GroupMap gm, int tiles_x, int tiles_y, const uint32_t* group_off,
                                 const uint32_t* wgbase, uint64_t* tmp_pair, uint16_t* tmp_code, int64_t capacity,

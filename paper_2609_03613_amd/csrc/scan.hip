@@ -634,10 +634,14 @@ __global__ void __launch_bounds__(kThreads) seg_base_kernel(const int32_t* __res
 // (one workgroup; G <= kMaxGroups = 8 per thread), and order[0 .. G) = the
 // groups by decreasing floor(log2(count)) (empty groups last; arbitrary
 // inside a class), so that the group sort starts the longest groups first.
+// A count of 2^32 entries or more wraps the prefix sums, and a position can then
+// belong to two groups: every group is empty instead (the stream is flagged as
+// truncated).
 // With sp.list, also the slices of kSlice entries of the groups that are
 // split, sp.list[i] = {group, index among the split groups, begin, end}, and
 // sp.ctl [0] = split groups, [1] = slices.
 __global__ void __launch_bounds__(kTailThreads) group_scan_kernel(const uint32_t* __restrict__ gcount, GroupMap gm,
+                                                                  const int64_t* __restrict__ counters,
                                                                   uint32_t* __restrict__ group_off,
                                                                   uint32_t* __restrict__ order, int64_t capacity,
                                                                   GroupSplit sp) {
@@ -660,10 +664,12 @@ __global__ void __launch_bounds__(kTailThreads) group_scan_kernel(const uint32_t
     if (threadIdx.x < kClasses) chist[threadIdx.x] = 0;
     // consecutive groups per thread, as few as cover them
     const int per = (G + kTailThreads - 1) / kTailThreads, i0 = per * threadIdx.x;
+    const bool wrapped = (uint64_t)counters[0] >> 32 != 0;
     uint32_t v[8], s = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         v[j] = j < per && i0 + j < G ? gcount[i0 + j] : 0u;
+        if (wrapped) v[j] = 0;
         s += v[j];
     }
     uint32_t total;
@@ -706,8 +712,6 @@ __global__ void __launch_bounds__(kTailThreads) group_scan_kernel(const uint32_t
             group_id[h++] = (uint16_t)(i0 + j);
             at += (n[j] + kSlice - 1) / kSlice;
         }
-        // (only an entry count that wrapped can exceed the bounds)
-        if (all_s > (uint32_t)sp.max_slices || all_g > (uint32_t)sp.max_groups) all_s = all_g = 0;
         if (threadIdx.x == 0) {
             sp.ctl[0] = all_g;
             sp.ctl[1] = all_s;
@@ -1328,9 +1332,10 @@ hipError_t launch_repair_select(const uint32_t* bin_off, int64_t T, int K, float
     return hipGetLastError();
 }
 
-hipError_t launch_group_scan(const uint32_t* gcount, GroupMap gm, uint32_t* group_off, uint32_t* order,
-                             int64_t capacity, const GroupSplit& sp, hipStream_t s) {
-    hipLaunchKernelGGL(group_scan_kernel, dim3(1), dim3(kTailThreads), 0, s, gcount, gm, group_off, order, capacity, sp);
+hipError_t launch_group_scan(const uint32_t* gcount, GroupMap gm, const int64_t* counters, uint32_t* group_off,
+                             uint32_t* order, int64_t capacity, const GroupSplit& sp, hipStream_t s) {
+    hipLaunchKernelGGL(group_scan_kernel, dim3(1), dim3(kTailThreads), 0, s, gcount, gm, counters, group_off, order,
+                       capacity, sp);
     return hipGetLastError();
 }
 
