@@ -302,8 +302,9 @@ TGS_API size_t tgs_bin_workspace_size(int64_t n, int64_t capacity, const tgs_cam
    bits and the binning is grouped);
    non-NULL = wait for the entry count, store it there, and return
    TGS_ERR_CAPACITY without building the stream when it exceeds capacity
-   (nothing uses the outputs any more then). Otherwise the rest of the BINNED
-   stream is built behind the call, as without the count. Not under capture.
+   (the outputs other than counters stay as they were, and nothing uses them
+   any more). Otherwise the rest of the BINNED stream is built behind the
+   call, as without the count. Not under capture.
    GLOBAL order without the host count: the radix sort runs over all
    `capacity` slots, those past the entry count padded with keys past the
    last tile (they stay out of the tile ranges), so its cost follows the

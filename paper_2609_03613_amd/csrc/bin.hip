@@ -101,9 +101,10 @@ __device__ __forceinline__ void depth_range_block(const uint4* __restrict__ info
                                                   const int64_t* __restrict__ counters, const NearKey& nk, int S,
                                                   float p_lo, float p_hi, float pad, float znear, float zfar,
                                                   float* __restrict__ zrange, const uint32_t* __restrict__ samples,
-                                                  RangeLds& R) {
+                                                  const int64_t* __restrict__ stop, RangeLds& R) {
 #pragma clang fp contract(off)
     const int64_t V = counters[1];
+    if (stopped(stop)) return;
     const int n = (int)(V < S ? V : S);
     if (n == 0) {
         if (threadIdx.x == 0) {
@@ -214,9 +215,10 @@ __global__ void __launch_bounds__(kRangeThreads) depth_range_kernel(const uint4*
                                                                    const int64_t* __restrict__ counters, NearKey nk,
                                                                    int S, float p_lo, float p_hi, float pad,
                                                                    float znear, float zfar, float* __restrict__ zrange,
-                                                                   const uint32_t* __restrict__ samples) {
+                                                                   const uint32_t* __restrict__ samples,
+                                                                   const int64_t* __restrict__ stop) {
     __shared__ RangeLds R;
-    depth_range_block(info, vis_ids, counters, nk, S, p_lo, p_hi, pad, znear, zfar, zrange, samples, R);
+    depth_range_block(info, vis_ids, counters, nk, S, p_lo, p_hi, pad, znear, zfar, zrange, samples, stop, R);
 }
 
 __device__ __forceinline__ void wave_sync() {
@@ -375,7 +377,7 @@ __global__ void __launch_bounds__(256) bin_count_kernel(const uint4* __restrict_
                                                         int64_t nseg,
                                                         uint32_t* __restrict__ entry_rank, int64_t capacity,
                                                         const int64_t* __restrict__ stop) {
-    if (stop && stop[2]) return;
+    if (stopped(stop)) return;
     __shared__ WaveGauss wg[4];
     const uint32_t x = (uint32_t)xcc_id() % (uint32_t)kCopies;
     const int64_t S = VAR ? (int64_t)sm.seg_base[(int64_t)tiles_x * tiles_y] : nseg;
@@ -414,7 +416,7 @@ __global__ void __launch_bounds__(256) bin_scatter_kernel(const uint4* __restric
                                                           const uint32_t* __restrict__ entry_rank,
                                                           uint64_t* __restrict__ pairs, int64_t capacity,
                                                           RecordSink rs, const int64_t* __restrict__ stop) {
-    if (stop && stop[2]) return;
+    if (stopped(stop)) return;
     __shared__ WaveGauss wg[4];
     const int64_t S = VAR ? (int64_t)sm.seg_base[(int64_t)tiles_x * tiles_y] : nseg;
     constexpr int R = kExpandRounds;
@@ -494,10 +496,10 @@ __global__ void __launch_bounds__(kCountThreads) group_count_kernel(const uint4*
     } U;
     if (blockIdx.x == 0) {
         depth_range_block(info, ra.vis_ids, ra.counters, ra.nk, ra.S, ra.p_lo, ra.p_hi, ra.pad, ra.znear, ra.zfar,
-                          ra.zrange, ra.samples, U.r);
+                          ra.zrange, ra.samples, ra.stop, U.r);
         return;
     }
-    if (ra.stop && ra.stop[2]) return;
+    if (stopped(ra.stop)) return;
     const int64_t chunk = blockIdx.x - 1;
     uint32_t* hist = U.c.hist;
     for (int g = threadIdx.x; g < gm.G; g += kCountThreads) hist[g] = 0;
@@ -540,7 +542,7 @@ __global__ void __launch_bounds__(kScatterThreads) group_scatter_kernel(const ui
                                                             uint64_t* __restrict__ tmp_pair,
                                                             uint16_t* __restrict__ tmp_code, int64_t capacity,
                                                             GroupSplit sp, const int64_t* __restrict__ stop) {
-    if (stop && stop[2]) return;
+    if (stopped(stop)) return;
     constexpr int NT = kScatterThreads, NW = NT / kWave;
     if (sp.list) {
         const int64_t words = (int64_t)sp.ctl[0] * sp.stride;
@@ -901,6 +903,7 @@ __global__ void __launch_bounds__(kLargeThreads) sort_large_kernel(const uint32_
                                                                    RepairSum sum) {
     __shared__ LargeLds lds;
     const uint32_t counts[3] = {bucket_count[5], bucket_count[6], bucket_count[7]};
+    const bool off = stopped(to.stop);
     for (int bucket = 5; bucket <= 7; ++bucket) {
         for (uint32_t i = blockIdx.x; i < counts[bucket - 5]; i += gridDim.x) {
             const int64_t at = (int64_t)bucket * nseg + i;
@@ -916,12 +919,12 @@ __global__ void __launch_bounds__(kLargeThreads) sort_large_kernel(const uint32_
     // the tile order's placement, by the last workgroups (the first ones
     // take the long segments)
     const int64_t c0 = (int64_t)gridDim.x - 1 - blockIdx.x;
-    if (to.order) {
+    if (to.order && !off) {
         const int64_t chunks = (to.T + kLargeThreads - 1) / kLargeThreads;
         if (c0 < chunks && to.counts) tile_hist_all<kLargeThreads>(to, lds.place);
         for (int64_t c = c0; c < chunks; c += gridDim.x) tile_place_chunk<kLargeThreads>(to, c, lds.place);
     }
-    if (sum.queued && blockIdx.x == 0) {
+    if (sum.queued && !off && blockIdx.x == 0) {
         constexpr int NW = kLargeThreads / kWave;
         __shared__ uint64_t part[NW];
         uint64_t s = 0;
@@ -970,7 +973,9 @@ __device__ __forceinline__ uint32_t tile_count(const uint32_t* offsets, const Se
 }
 
 __global__ void __launch_bounds__(256) tile_hist_kernel(const uint32_t* __restrict__ offsets, SegMap sm, int64_t T,
-                                                        uint32_t* __restrict__ hist) {
+                                                        uint32_t* __restrict__ hist,
+                                                        const int64_t* __restrict__ stop) {
+    if (stopped(stop)) return;
     __shared__ uint32_t h[kOrderBuckets];
     if (threadIdx.x < kOrderBuckets) h[threadIdx.x] = 0;
     __syncthreads();
@@ -1070,6 +1075,7 @@ __device__ __forceinline__ void tile_place_chunk(const TileOrder& to, int64_t ch
 }
 
 __global__ void __launch_bounds__(256) tile_place_kernel(TileOrder to) {
+    if (stopped(to.stop)) return;
     __shared__ PlaceLds L;
     if (to.counts) tile_hist_all<256>(to, L);
     tile_place_chunk<256>(to, blockIdx.x, L);
@@ -1134,12 +1140,12 @@ inline unsigned grid_for(int64_t n, int block) { return (unsigned)((n + block - 
 
 hipError_t launch_depth_range(const uint32_t* info, const uint32_t* vis_ids, const int64_t* counters, NearKey nk,
                               int S, float p_lo, float p_hi, float pad, float znear, float zfar, float* zrange,
-                              uint32_t* samples, hipStream_t s) {
+                              uint32_t* samples, const int64_t* stop, hipStream_t s) {
     const auto* in = reinterpret_cast<const uint4*>(info);
     hipLaunchKernelGGL(range_samples_kernel, dim3((unsigned)((S + 255) / 256)), dim3(256), 0, s, in, vis_ids, counters,
                        nk, S, samples);
     hipLaunchKernelGGL(depth_range_kernel, dim3(1), dim3(kRangeThreads), 0, s, in, vis_ids, counters, nk, S, p_lo, p_hi,
-                       pad, znear, zfar, zrange, samples);
+                       pad, znear, zfar, zrange, samples, stop);
     return hipGetLastError();
 }
 
@@ -1196,11 +1202,11 @@ hipError_t launch_repair(const uint32_t* bin_off, int64_t nseg, uint64_t* pairs,
 }
 
 hipError_t launch_tile_order(const uint32_t* offsets, SegMap sm, int64_t T, uint32_t* hist, uint32_t* order, int split,
-                             int factor, hipStream_t s) {
+                             int factor, const int64_t* stop, hipStream_t s) {
     if (T == 0) return hipSuccess;
-    hipLaunchKernelGGL(tile_hist_kernel, dim3(grid_for(T, 256)), dim3(256), 0, s, offsets, sm, T, hist);
+    hipLaunchKernelGGL(tile_hist_kernel, dim3(grid_for(T, 256)), dim3(256), 0, s, offsets, sm, T, hist, stop);
     hipLaunchKernelGGL(tile_place_kernel, dim3(grid_for(T, 256)), dim3(256), 0, s,
-                       TileOrder{offsets, sm, T, hist, order, split, factor, nullptr});
+                       TileOrder{offsets, sm, T, hist, order, split, factor, nullptr, stop});
     return hipGetLastError();
 }
 

@@ -524,8 +524,8 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
     // for in between, the device idled for 33 us until the host had come back
     // and launched the next kernel (a frame of 2 thousand Gaussians on 128x128
     // 128 us, now 75; of one million on 1920x1080 385 us, now 352). When the
-    // entries exceed the capacity, the kernels that expand them return at once
-    // (stop), the stream that was launched meanwhile is empty and waited for.
+    // entries exceed the capacity, the kernels launched meanwhile expand nothing
+    // and write no output (stop), and they are waited for.
     const int64_t* stop = num_entries_host ? out->counters_dev : nullptr;
     auto read_count = [&]() -> tgs_status {
         if (!num_entries_host) return TGS_OK;
@@ -555,7 +555,7 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
         TGS_HIP(launch_tile_ranges(out->keys_dev, sort_n, T, out->offsets_dev, s), "tile ranges");
         if (out->tile_order_dev)
             TGS_HIP(launch_tile_order(out->offsets_dev, SegMap{nullptr, 1, nullptr}, T, zero + kTileHist,
-                                      out->tile_order_dev, params->split_entries, params->split_mean_factor, s),
+                                      out->tile_order_dev, params->split_entries, params->split_mean_factor, nullptr, s),
                     "tile order");
         return TGS_OK;
     }
@@ -572,10 +572,10 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
                   params->packed ? out->masks_dev : nullptr, K, tiles_x, cam->width, cam->height};
     if (var) {
         TGS_HIP(launch_seg_base(params->per_tile_bins_dev, T, K, out->seg_base_dev, tile_seg, zero + kTicketSegs,
-                                (uint64_t*)(zero + L.status_segs), s),
+                                (uint64_t*)(zero + L.status_segs), stop, s),
                 "segment bases");
         if (L.gm.G == 0)
-            TGS_HIP(launch_fill_u32_dyn(count, 0u, nseg_dev, kCopies, (int64_t)kCopies * nseg, s), "clear counts");
+            TGS_HIP(launch_fill_u32_dyn(count, 0u, nseg_dev, kCopies, (int64_t)kCopies * nseg, stop, s), "clear counts");
     }
     const float zn = (float)cam->znear, zf = (float)cam->zfar;
     const NearKey nk{params->near_shift ? reinterpret_cast<const float4*>(pr->splats_dev) : nullptr,
@@ -618,18 +618,18 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
         // tile order's own two launches.
         uint32_t* tile_count = out->tile_order_dev && T <= kCountedTiles ? (uint32_t*)(w + L.tile_count) : nullptr;
         const TileOrder to{out->offsets_dev, sm, T, zero + kTileHist, tile_count ? out->tile_order_dev : nullptr,
-                           params->split_entries, params->split_mean_factor, tile_count};
+                           params->split_entries, params->split_mean_factor, tile_count, stop};
         uint32_t* queued = (uint32_t*)(w + L.queued);
         const bool all = params->repair == TGS_REPAIR_ALL;
         const RepairSum sum{all ? queued : nullptr, gm.G, out->counters_dev};
         TGS_HIP(launch_group_sort(tmp_pair, tmp_code, group_off, group_order, out->zrange_dev, gm, nseg, cap, out->pairs_dev,
                                   out->offsets_dev, seg_lists, L.list_stride, bucket_count, out->counters_dev, all,
-                                  out->repaired_dev, rs, queued, tile_count, sp, (uint16_t*)(w + L.part_tile), s),
+                                  out->repaired_dev, rs, queued, tile_count, sp, (uint16_t*)(w + L.part_tile), stop, s),
                 "group sort");
         if (rules)
             TGS_HIP(launch_repair_select(out->offsets_dev, T, K, params->repair_budget, zero + kTicketSel,
                                          (uint64_t*)(zero + L.status_sel), zero + kSelCtl, seg_lists, bucket_count,
-                                         out->counters_dev, out->repaired_dev, s),
+                                         out->counters_dev, out->repaired_dev, stop, s),
                     "repair selection");
         // with sub-bins the queues hold sub-segment descriptors
         if (params->repair != TGS_REPAIR_NONE)
@@ -640,24 +640,24 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
             TGS_HIP(launch_tile_place(to, s), "tile order");
         if (out->tile_order_dev && !tile_count)
             TGS_HIP(launch_tile_order(out->offsets_dev, sm, T, zero + kTileHist, out->tile_order_dev,
-                                      params->split_entries, params->split_mean_factor, s),
+                                      params->split_entries, params->split_mean_factor, stop, s),
                     "tile order");
         return read_count();
     }
     TGS_HIP(launch_depth_range(pr->info_dev, vis_ids, out->counters_dev, nk, S, params->p_lo, params->p_hi,
-                               params->pad, zn, zf, out->zrange_dev, (uint32_t*)(w + L.samples), s),
+                               params->pad, zn, zf, out->zrange_dev, (uint32_t*)(w + L.samples), stop, s),
             "depth range");
     TGS_HIP(launch_bin_count(pr->info_dev, n, emit_off, out->zrange_dev, nk, sm, tiles_x, tiles_y, count, nseg,
                              entry_rank, cap, stop, s),
             "bin count");
     TGS_HIP(launch_bin_offsets(count, nseg, nseg_dev, out->offsets_dev, zero + kTicketBins,
                                (uint64_t*)(zero + L.status_bins), seg_lists, bucket_count, out->counters_dev,
-                               params->repair == TGS_REPAIR_ALL, out->repaired_dev, s),
+                               params->repair == TGS_REPAIR_ALL, out->repaired_dev, stop, s),
             "bin offsets");
     if (rules)
         TGS_HIP(launch_repair_select(out->offsets_dev, T, K, params->repair_budget, zero + kTicketSel,
                                      (uint64_t*)(zero + L.status_sel), zero + kSelCtl, seg_lists, bucket_count,
-                                     out->counters_dev, out->repaired_dev, s),
+                                     out->counters_dev, out->repaired_dev, stop, s),
                 "repair selection");
     TGS_HIP(launch_bin_scatter(pr->info_dev, n, emit_off, out->zrange_dev, nk, sm, tiles_x, tiles_y, out->offsets_dev,
                                count, nseg, entry_rank, out->pairs_dev, cap, rs, stop, s),
@@ -668,7 +668,7 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
                 "repair");
     if (out->tile_order_dev)
         TGS_HIP(launch_tile_order(out->offsets_dev, sm, T, zero + kTileHist, out->tile_order_dev,
-                                  params->split_entries, params->split_mean_factor, s),
+                                  params->split_entries, params->split_mean_factor, stop, s),
                 "tile order");
     return read_count();
 }

@@ -99,6 +99,12 @@ struct DepthBins {
     }
 };
 
+// Whether a call that returns the entry count to the host found more entries
+// than the capacity (stop: its counters, null without the host count). Nothing
+// is expanded then, and no output but the counters is written: a stream that
+// the buffers hold stays as it is.
+__device__ __forceinline__ bool stopped(const int64_t* stop) { return stop && stop[2] != 0; }
+
 // XCD (accelerator complex die) executing the calling wave, 0..7.
 __device__ __forceinline__ int xcc_id() {
     return (int)(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & 7u);
@@ -408,7 +414,7 @@ hipError_t launch_emit_scan(const uint32_t* info, int64_t n, int tiles_x, int ti
 // their keys.
 hipError_t launch_depth_range(const uint32_t* info, const uint32_t* vis_ids, const int64_t* counters, NearKey nk,
                               int S, float p_lo, float p_hi, float pad, float znear, float zfar, float* zrange,
-                              uint32_t* samples, hipStream_t s);
+                              uint32_t* samples, const int64_t* stop, hipStream_t s);
 // The arguments of the depth range, for the launch that runs it beside the
 // group count.
 struct RangeArgs {
@@ -458,7 +464,8 @@ __host__ __device__ __forceinline__ int bucket_of(uint32_t len) {
 // [scan_blocks(nseg)] and bucket_count must be zero.
 hipError_t launch_bin_offsets(uint32_t* count, int64_t nseg, const uint32_t* nseg_dev, uint32_t* bin_off,
                               uint32_t* ticket, uint64_t* status, uint32_t* lists, uint32_t* bucket_count,
-                              int64_t* counters, bool queue_all, uint8_t* repaired, hipStream_t s);
+                              int64_t* counters, bool queue_all, uint8_t* repaired, const int64_t* stop,
+                              hipStream_t s);
 // Rule-based repair selection over the T * K segments (uniform K): the
 // keep rules per segment, the prefix of the kept lengths by a single-pass
 // scan (segments whose inclusive prefix is within the budget are queued as
@@ -468,7 +475,7 @@ hipError_t launch_bin_offsets(uint32_t* count, int64_t nseg, const uint32_t* nse
 // selected entries.
 hipError_t launch_repair_select(const uint32_t* bin_off, int64_t T, int K, float budget, uint32_t* ticket,
                                 uint64_t* status, uint32_t* ctl, uint32_t* lists, uint32_t* bucket_count,
-                                int64_t* counters, uint8_t* repaired, hipStream_t s);
+                                int64_t* counters, uint8_t* repaired, const int64_t* stop, hipStream_t s);
 hipError_t launch_bin_scatter(const uint32_t* info, int64_t n, const uint32_t* emit_off, const float* zrange,
                               NearKey nk, SegMap sm, int tiles_x, int tiles_y, const uint32_t* bin_off,
                               const uint32_t* base, int64_t nseg, const uint32_t* entry_rank, uint64_t* pairs,
@@ -509,7 +516,7 @@ hipError_t launch_group_sort(const uint64_t* tmp_pair, uint16_t* tmp_code, const
                              uint32_t* lists, int64_t list_stride, uint32_t* bucket_count,
                              const int64_t* counters, bool queue_all, uint8_t* repaired, RecordSink rs,
                              uint32_t* queued, uint32_t* tile_count, const GroupSplit& sp, uint16_t* part_tile,
-                             hipStream_t s);
+                             const int64_t* stop, hipStream_t s);
 
 // Per-tile bin counts: seg_base[t] = exclusive prefix sum of the bin counts
 // (each clamped to 1..kmax and rounded down to a power of two), seg_base[T]
@@ -517,10 +524,10 @@ hipError_t launch_group_sort(const uint64_t* tmp_pair, uint16_t* tmp_code, const
 // kernels (one 8-byte load per entry). ticket and status [scan_blocks(T)]
 // must be zero.
 hipError_t launch_seg_base(const int32_t* per_tile_bins, int64_t T, int kmax, uint32_t* seg_base, uint2* tile_seg,
-                           uint32_t* ticket, uint64_t* status, hipStream_t s);
+                           uint32_t* ticket, uint64_t* status, const int64_t* stop, hipStream_t s);
 // p[0 .. mult * *n_dev) = v.
 hipError_t launch_fill_u32_dyn(uint32_t* p, uint32_t v, const uint32_t* n_dev, int mult, int64_t max_n,
-                               hipStream_t s);
+                               const int64_t* stop, hipStream_t s);
 
 // Placement half of the tile order (launch_tile_order below). counts ==
 // null: over a histogram that is already complete, hist [33] per bit-length
@@ -535,6 +542,7 @@ struct TileOrder {
     uint32_t* order;
     int split, factor;
     const uint32_t* counts;
+    const int64_t* stop;
 };
 constexpr int64_t kCountedTiles = 65536;
 // counters[3] = the sum of queued [G] (null: nothing to sum).
@@ -565,7 +573,7 @@ hipError_t launch_tile_place(const TileOrder& to, hipStream_t s);
 constexpr int kSplitTiles = 1024;
 constexpr int kFillWaves = 256 * 32;  // wavefronts the 256 CUs hold at 8 per SIMD
 hipError_t launch_tile_order(const uint32_t* offsets, SegMap sm, int64_t T, uint32_t* hist, uint32_t* order, int split,
-                             int factor, hipStream_t s);
+                             int factor, const int64_t* stop, hipStream_t s);
 
 hipError_t launch_emit_keys(const uint32_t* info, int64_t n, const uint32_t* emit_off, int tiles_x, int tiles_y,
                             uint64_t* keys, uint32_t* vals, int64_t capacity, hipStream_t s);

@@ -334,7 +334,9 @@ __global__ void __launch_bounds__(kThreads) bin_offsets_kernel(uint32_t* __restr
                                                                uint64_t* status, uint32_t* __restrict__ lists,
                                                                uint32_t* __restrict__ bucket_count,
                                                                int64_t* __restrict__ counters, bool queue_all,
-                                                               uint8_t* __restrict__ repaired) {
+                                                               uint8_t* __restrict__ repaired,
+                                                               const int64_t* __restrict__ stop) {
+    if (stopped(stop)) return;  // the segment bases were not written either
     __shared__ uint32_t tk;
     __shared__ uint32_t lds32[kThreads / kWave];
     __shared__ uint64_t pre;
@@ -449,7 +451,9 @@ __global__ void __launch_bounds__(kThreads) select_prefix_kernel(const uint32_t*
                                                                  uint32_t* __restrict__ lists,
                                                                  uint32_t* __restrict__ bucket_count,
                                                                  int64_t* __restrict__ counters,
-                                                                 uint8_t* __restrict__ repaired) {
+                                                                 uint8_t* __restrict__ repaired,
+                                                                 const int64_t* __restrict__ stop) {
+    if (stopped(stop)) return;
     __shared__ uint32_t tk;
     __shared__ uint32_t lds32[kThreads / kWave];
     __shared__ uint64_t pre;
@@ -590,7 +594,9 @@ __device__ __forceinline__ uint32_t pow2_bins(int32_t k, int kmax) {
 
 __global__ void __launch_bounds__(kThreads) seg_base_kernel(const int32_t* __restrict__ kt, int64_t T, int kmax,
                                                             uint32_t* __restrict__ seg_base, uint2* __restrict__ tile_seg,
-                                                            uint32_t* ticket, uint64_t* status) {
+                                                            uint32_t* ticket, uint64_t* status,
+                                                            const int64_t* __restrict__ stop) {
+    const bool write = !stopped(stop);
     __shared__ uint32_t tk;
     __shared__ uint32_t lds32[kThreads / kWave];
     __shared__ uint64_t pre;
@@ -614,14 +620,14 @@ __global__ void __launch_bounds__(kThreads) seg_base_kernel(const int32_t* __res
     }
     __syncthreads();
     uint32_t carry = (uint32_t)pre;
-    if (b == nb - 1 && threadIdx.x == 0) seg_base[T] = carry + agg;
+    if (write && b == nb - 1 && threadIdx.x == 0) seg_base[T] = carry + agg;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
         const int64_t t = base + r * kThreads + threadIdx.x;
         uint32_t tot;
         const uint32_t ex = block_excl_u32(v[r], lds32, &tot);
         if (t < T) {
-            seg_base[t] = carry + ex;
+            if (write) seg_base[t] = carry + ex;
             tile_seg[t] = make_uint2(carry + ex, 32u - (uint32_t)__builtin_ctz(v[r]));
         }
         carry += tot;
@@ -913,7 +919,7 @@ __global__ void __launch_bounds__(kSortThreads, 4) group_sort_kernel(
     uint32_t* __restrict__ bin_off, uint32_t* __restrict__ lists, int64_t list_stride,
     uint32_t* __restrict__ bucket_count, const int64_t* __restrict__ counters, bool queue_all,
     uint8_t* __restrict__ repaired, RecordSink rs, uint32_t* __restrict__ queued, uint32_t* __restrict__ tile_count,
-    GroupSplit sp) {
+    GroupSplit sp, const int64_t* __restrict__ stop) {
     constexpr int NT = kSortThreads;
     constexpr int kMaxPer = kMaxGroupSegs / NT;
     constexpr uint32_t kNone = 0xFFFFFFFFu;
@@ -985,6 +991,7 @@ __global__ void __launch_bounds__(kSortThreads, 4) group_sort_kernel(
     if (sp.list && split_group(hi - lo)) return;
     const GroupCodes gc = codes_of(gm, g, nseg);
     if (lo == hi) {  // an empty group: offsets only
+        if (stopped(stop)) return;  // (all groups are empty then)
         for (int c = threadIdx.x; c < gc.segs; c += NT) {
             bin_off[gc.sbase + c] = lo;
             if (repaired) repaired[gc.sbase + c] = 0;
@@ -1287,7 +1294,8 @@ __global__ void __launch_bounds__(kSplitThreads) group_split_kernel(
     }
 }
 
-__global__ void fill_u32_dyn_kernel(uint32_t* p, uint32_t v, const uint32_t* n_dev, int mult) {
+__global__ void fill_u32_dyn_kernel(uint32_t* p, uint32_t v, const uint32_t* n_dev, int mult, const int64_t* stop) {
+    if (stopped(stop)) return;  // *n_dev was not written
     const int64_t n = (int64_t)*n_dev * mult;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = v;
@@ -1314,19 +1322,20 @@ hipError_t launch_emit_scan(const uint32_t* info, int64_t n, int tiles_x, int ti
 
 hipError_t launch_bin_offsets(uint32_t* count, int64_t nseg, const uint32_t* nseg_dev, uint32_t* bin_off,
                               uint32_t* ticket, uint64_t* status, uint32_t* lists, uint32_t* bucket_count,
-                              int64_t* counters, bool queue_all, uint8_t* repaired, hipStream_t s) {
+                              int64_t* counters, bool queue_all, uint8_t* repaired, const int64_t* stop,
+                              hipStream_t s) {
     hipLaunchKernelGGL(bin_offsets_kernel, dim3((unsigned)scan_blocks(nseg)), dim3(kThreads), 0, s, count, nseg,
-                       nseg_dev, bin_off, ticket, status, lists, bucket_count, counters, queue_all, repaired);
+                       nseg_dev, bin_off, ticket, status, lists, bucket_count, counters, queue_all, repaired, stop);
     return hipGetLastError();
 }
 
 hipError_t launch_repair_select(const uint32_t* bin_off, int64_t T, int K, float budget, uint32_t* ticket,
                                 uint64_t* status, uint32_t* ctl, uint32_t* lists, uint32_t* bucket_count,
-                                int64_t* counters, uint8_t* repaired, hipStream_t s) {
+                                int64_t* counters, uint8_t* repaired, const int64_t* stop, hipStream_t s) {
     const int64_t nseg = T * K;
     if (nseg == 0) return hipSuccess;
     hipLaunchKernelGGL(select_prefix_kernel, dim3((unsigned)scan_blocks(nseg)), dim3(kThreads), 0, s, bin_off, nseg,
-                       K, budget, ticket, status, ctl, lists, bucket_count, counters, repaired);
+                       K, budget, ticket, status, ctl, lists, bucket_count, counters, repaired, stop);
     hipLaunchKernelGGL(select_tail_kernel, dim3(1), dim3(kTailThreads), 0, s, bin_off, nseg, K, budget, ctl, lists,
                        bucket_count, counters, repaired);
     return hipGetLastError();
@@ -1344,10 +1353,10 @@ hipError_t launch_group_sort(const uint64_t* tmp_pair, uint16_t* tmp_code, const
                              uint32_t* lists, int64_t list_stride, uint32_t* bucket_count,
                              const int64_t* counters, bool queue_all, uint8_t* repaired, RecordSink rs,
                              uint32_t* queued, uint32_t* tile_count, const GroupSplit& sp, uint16_t* part_tile,
-                             hipStream_t s) {
+                             const int64_t* stop, hipStream_t s) {
     hipLaunchKernelGGL(gm.tagged ? group_sort_kernel<true> : group_sort_kernel<false>, dim3((unsigned)(sp.slice_grid + gm.G)), dim3(kSortThreads), 0, s, tmp_pair,
                        tmp_code, group_off, order, zrange, gm, nseg, capacity, pairs, bin_off, lists, list_stride, bucket_count,
-                       counters, queue_all, repaired, rs, queued, tile_count, sp);
+                       counters, queue_all, repaired, rs, queued, tile_count, sp, stop);
     if (sp.list) {
         hipLaunchKernelGGL(gm.tagged ? group_split_kernel<true> : group_split_kernel<false>, dim3((unsigned)std::min(sp.max_slices, kSplitGrid)),
                            dim3(kSplitThreads), 0, s, tmp_pair, tmp_code, group_off, zrange, gm, nseg, capacity, pairs,
@@ -1357,18 +1366,18 @@ hipError_t launch_group_sort(const uint64_t* tmp_pair, uint16_t* tmp_code, const
 }
 
 hipError_t launch_seg_base(const int32_t* per_tile_bins, int64_t T, int kmax, uint32_t* seg_base, uint2* tile_seg,
-                           uint32_t* ticket, uint64_t* status, hipStream_t s) {
+                           uint32_t* ticket, uint64_t* status, const int64_t* stop, hipStream_t s) {
     hipLaunchKernelGGL(seg_base_kernel, dim3((unsigned)scan_blocks(T)), dim3(kThreads), 0, s, per_tile_bins, T, kmax,
-                       seg_base, tile_seg, ticket, status);
+                       seg_base, tile_seg, ticket, status, stop);
     return hipGetLastError();
 }
 
 hipError_t launch_fill_u32_dyn(uint32_t* p, uint32_t v, const uint32_t* n_dev, int mult, int64_t max_n,
-                               hipStream_t s) {
+                               const int64_t* stop, hipStream_t s) {
     if (max_n <= 0) return hipSuccess;
     int64_t grid = (max_n + 255) / 256;
     if (grid > 4096) grid = 4096;
-    hipLaunchKernelGGL(fill_u32_dyn_kernel, dim3((unsigned)grid), dim3(256), 0, s, p, v, n_dev, mult);
+    hipLaunchKernelGGL(fill_u32_dyn_kernel, dim3((unsigned)grid), dim3(256), 0, s, p, v, n_dev, mult, stop);
     return hipGetLastError();
 }
 
