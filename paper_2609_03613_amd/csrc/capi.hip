@@ -201,7 +201,7 @@ Layout layout(int64_t n, int64_t capacity, int64_t T, int K, int order, bool var
     L.list_stride = nseg;
     if (grouped) {
         L.gm.chunk = group_chunk(n);
-        const size_t chunks = (size_t)((n + L.gm.chunk - 1) / L.gm.chunk);
+        const size_t chunks = (size_t)most_chunks(n);
         size_t entry = sizeof(uint32_t);
         // groups are split with sub-bins (exact repair without records), when
         // the capacity allows groups that long

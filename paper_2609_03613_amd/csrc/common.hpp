@@ -286,6 +286,14 @@ inline int group_chunk(int64_t n) {
     while (c > 256 && (n + c - 1) / c < kMinChunks) c /= 2;
     return c;
 }
+// At least the workgroups of any scene of up to n Gaussians (the chunk halves
+// below kMinChunks workgroups, so a smaller scene can have twice as many): a
+// workspace sized for n holds every smaller one.
+inline int64_t most_chunks(int64_t n) {
+    const int64_t c = group_chunk(n), fine = (n + 255) / 256;
+    const int64_t chunks = (n + c - 1) / c, bound = fine < 2 * kMinChunks ? fine : 2 * kMinChunks;
+    return chunks > bound ? chunks : bound;
+}
 // The grouped path's group shape for T tiles and K bins: GT = max(1,
 // kGroupSegTarget / K) tiles, doubled until G <= kMaxGroups; .G = 0 when GS
 // would exceed kMaxGroupSegs (then the per-entry atomic path is used). SB =

@@ -1,5 +1,6 @@
 """The workspace of tgs_bin (sizes only, no GPU): the repair lists hold every
-run that the parts of split groups can queue."""
+run that the parts of split groups can queue, and a workspace sized for n
+Gaussians and a capacity holds every smaller n and capacity."""
 import ctypes
 
 import numpy as np
@@ -28,3 +29,19 @@ def test_repair_lists_grow_with_the_buckets_of_long_parts(width, bins, sub):
     grown = workspace(1000, c1, width, 16, num_bins=bins, sub_bins=sub) - workspace(
         1000, c0, width, 16, num_bins=bins, sub_bins=sub)
     assert grown >= (c1 - c0) * 12 + 8 * 8 * ((c1 - c0) // 513) - 4096
+
+
+@pytest.mark.parametrize("width, height, params", [
+    (4096, 4096, dict(num_bins=64, tile_size=16)),               # 8192 groups
+    (1920, 1080, dict()),
+    (640, 360, dict(num_bins=16, repair="rules")),
+    (1920, 1080, dict(num_bins=128, tile_size=32, sub_bins=2)),
+])
+def test_workspace_does_not_shrink(width, height, params):
+    edges = [0, 1, 255, 256, 257, 65024, 65025, 65536, 65537, 130048, 130049, 131072, 260096, 260097, 262144, 262145,
+             524288, 524289, 3_000_000]
+    ns = sorted(set(edges) | {int(1.07 ** k) for k in range(220)})
+    sizes = [workspace(n, 100_000, width, height, **params) for n in ns]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+    caps = [workspace(50_000, c, width, height, **params) for c in sorted({int(1.11 ** k) for k in range(200)})]
+    assert all(a <= b for a, b in zip(caps, caps[1:]))
