@@ -689,10 +689,10 @@ __device__ __forceinline__ void sort_small(const SmallSort& S, const uint32_t (&
 
 // The parts of the split groups (GroupSplit), one per workgroup, sorted in
 // place: bucket sort by tile and depth over the part's own depth range. A
-// bucket of up to kBucketRank pairs is ordered by rank; longer ones (depths
-// far more clustered than the range) are queued for the long-segment launch,
-// as is a part longer than the stage (a single code). The next part's entries
-// are in flight while one is written out.
+// bucket of more than kBucketMost pairs (depths far more clustered than the
+// range) is queued for the long-segment launch, as is a part longer than the
+// stage (a single code). The next part's entries are in flight while one is
+// written out.
 constexpr int kPartThreads = 1024;
 constexpr int kPartGrid = 512;          // two workgroups per CU: all its wavefronts
 constexpr int kPartCap = kPartStep + kPartCode;  // keys of the bucket sort
@@ -702,7 +702,7 @@ __device__ __forceinline__ void sort_parts(uint64_t* __restrict__ pairs, const u
                                            uint32_t* __restrict__ bucket_count, const GroupSplit& sp, PartLds& L) {
     constexpr int NT = kPartThreads, kEnt = kPartCap / NT;
     static_assert(kBucketSlots >= kMaxGroupSegs, "a bucket per tile");
-    static_assert(kBucketRank >= 512, "only buckets 5..7 are queued");
+    static_assert(kBucketMost >= 512, "only buckets 5..7 are queued");
     auto queue = [&](uint32_t begin, uint32_t len) {
         const int k = bucket_of(len);
         lists[(int64_t)k * list_stride + atomicAdd(&bucket_count[k], 1u)] = make_uint2(begin, len);
@@ -732,17 +732,17 @@ __device__ __forceinline__ void sort_parts(uint64_t* __restrict__ pairs, const u
 #pragma unroll
         for (int j = 0; j < kEnt; ++j) b[j] -= u.z;
         range_buckets(pr, b, u.w, L);
-        const bool clustered = place_buckets(pr, b, n, L);
+        const bool clustered = place_buckets(pr, b, n, L) == 2;
         load(it + gridDim.x);
         for (uint32_t q = threadIdx.x; q < n; q += NT) {
             const uint32_t k = L.bucket[q], at = L.off[k], len = L.off[k + 1] - at;
             const uint64_t v = L.stage[q];
-            pairs[lo + (len >= 2 && len <= (uint32_t)kBucketRank ? rank_slot(L.stage, v, at, len) : q)] = v;
+            pairs[lo + (len >= 2 && len <= (uint32_t)kBucketMost ? rank_slot(L.stage, v, at, len) : q)] = v;
         }
         if (clustered)
             for (int k = threadIdx.x; k < kBucketSlots; k += NT) {
                 const uint32_t at = L.off[k], len = L.off[k + 1] - at;
-                if (len > (uint32_t)kBucketRank) queue(lo + at, len);
+                if (len > (uint32_t)kBucketMost) queue(lo + at, len);
             }
         __syncthreads();
     }
@@ -793,29 +793,36 @@ union LargeLds {
     PlaceLds place;
 };
 
-// One segment of 513..8192 keys by the workgroup, E keys per thread: bucket
-// sort over the segment's own depth range, or, when some depths are too
-// clustered for it, the register / lane / LDS bitonic network of
-// sort_block_reg; coalesced loads and stores (with the records when !DESC).
-// The network makes 91 compare steps over 8192 keys, the bucket sort a few LDS
-// accesses per key: with a longest segment of 4295 keys (10 million Gaussians
-// on 1920x1080) this launch took 249 us, now 37.
+// One segment of 513..8192 keys by the workgroup, E keys per thread: above
+// kNetworkMost keys by bucket sort over the segment's own depth range, up to
+// it, or when a bucket holds more than kBucketMost keys, by the register / lane
+// / LDS bitonic network of sort_block_reg; coalesced loads and stores (with the
+// records when !DESC). The network makes 91 compare steps over 8192 keys, the
+// bucket sort a few LDS accesses per key: with a longest segment of 4295 keys
+// (10 million Gaussians on 1920x1080) this launch took 249 us, now 25.
+// Shorter segments are mostly those of the first and last bins, whose depths are
+// clustered: with buckets of up to 512 keys ordered by rank the launch took 38 us
+// for 500 thousand Gaussians in random order on 640x360, with a wavefront per
+// long bucket 16, with the network 8.5.
+constexpr int kNetworkMost = 2048;
 template <int E, bool DESC>
 __device__ __forceinline__ void sort_large_block(uint64_t* pairs, uint32_t s, uint32_t begin, uint32_t len,
                                                  const RecordSink& rs, LargeLds& lds) {
     constexpr uint32_t P = (uint32_t)kLargeThreads * E;
     uint64_t v[E];
-    {
+    if constexpr (E * kLargeThreads > kNetworkMost) {
         uint32_t b[E] = {};
 #pragma unroll
         for (int j = 0; j < E; ++j) v[j] = pairs[begin + min((uint32_t)(j * kLargeThreads) + threadIdx.x, len - 1)];
         BucketLds<kLargeThreads, kLargeCap>& L = lds.buckets;
-        range_buckets(v, b, 1u, L);
-        if (!place_buckets(v, b, len, L)) {
+        const bool apart = range_buckets(v, b, 1u, L);
+        const int clustered = apart ? place_buckets(v, b, len, L) : 2;
+        if (clustered < 2) {
+            if (clustered) sort_long_buckets(L);
             for (uint32_t q = threadIdx.x; q < len; q += kLargeThreads) {
                 const uint32_t k = L.bucket[q], at = L.off[k], n = L.off[k + 1] - at;
                 const uint64_t x = L.stage[q];
-                const uint32_t to = begin + (n >= 2 ? rank_slot(L.stage, x, at, n) : q);
+                const uint32_t to = begin + (n >= 2 && n <= (uint32_t)kBucketRank ? rank_slot(L.stage, x, at, n) : q);
                 pairs[to] = x;
                 if (!DESC) rs.put(s, to, x);
             }

@@ -209,9 +209,9 @@ Layout layout(int64_t n, int64_t capacity, int64_t T, int K, int order, bool var
         if (L.gm.SB > 1) {
             // queued as {begin, length}, disjoint runs of two or more of the at
             // most capacity entries: sub-segments, each once, and in the parts of
-            // split groups also buckets of more than kBucketRank entries, several
+            // split groups also buckets of more than kBucketMost entries, several
             // of which can come from one sub-segment
-            const int64_t buckets = split ? capacity / (kBucketRank + 1) : 0;
+            const int64_t buckets = split ? capacity / (kBucketMost + 1) : 0;
             L.list_stride = std::min<int64_t>(nseg * L.gm.SB + buckets, capacity / 2 + 1);
             entry = sizeof(uint2);
         }

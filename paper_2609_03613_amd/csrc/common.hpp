@@ -326,9 +326,9 @@ constexpr int kPartCode = 1024;    // a code of more entries is a part by itself
 // long (5 million Gaussians on 280x207, three groups of 1.4 million entries, with
 // room for 2048 parts, hence groups of at most 0.9 million: 1980 us, now 795)
 constexpr int kMaxParts = kMaxGroupSegs;
-// Longest bucket of a workgroup bucket sort that is ordered by rank; a longer one
-// of a part is queued for the long-segment sort.
-constexpr int kBucketRank = 512;
+// Longest bucket that a workgroup bucket sort orders itself; a longer one of a
+// part is queued for the long-segment sort.
+constexpr int kBucketMost = 512;
 constexpr uint32_t kSplitMin = 16384;
 constexpr int64_t kSplitMean = 4096;
 __host__ __device__ __forceinline__ bool split_group(uint32_t n) { return n > kSplitMin; }

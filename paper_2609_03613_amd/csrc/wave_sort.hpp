@@ -170,7 +170,12 @@ __device__ __forceinline__ void sort_block_reg(uint64_t (&v)[E], uint64_t* lds) 
 // bucket is its rank there. With the buckets spread over the keys' own range a
 // bucket holds one or two keys, so this is one LDS atomic, one LDS write and a
 // few LDS reads per key against the O(log^2) exchanges of the networks.
+// Where the keys are clustered in their range (the first and the last bin hold
+// the depths outside the percentiles) a rank takes as many LDS reads as the
+// bucket has keys, and buckets of more than kBucketRank keys can be ordered by a
+// wavefront's network each (sort_long_buckets).
 constexpr int kBucketSlots = 4096;
+constexpr int kBucketRank = 64;  // longest bucket ordered by rank
 
 template <int NT, int CAP>
 struct BucketLds {
@@ -184,9 +189,9 @@ struct BucketLds {
 // among the `tiles` tiles (b[j] holds the key's tile, 0 .. tiles - 1 <
 // kBucketSlots, on entry), and within a tile spread by a monotone map over the
 // range of all keys' upper words. Every register holds a key (repeated ones
-// past the last).
+// past the last). False when all upper words are equal.
 template <int E, int NT, int CAP>
-__device__ __forceinline__ void range_buckets(const uint64_t (&key)[E], uint32_t (&b)[E], uint32_t tiles,
+__device__ __forceinline__ bool range_buckets(const uint64_t (&key)[E], uint32_t (&b)[E], uint32_t tiles,
                                               BucketLds<NT, CAP>& L) {
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
@@ -218,13 +223,15 @@ __device__ __forceinline__ void range_buckets(const uint64_t (&key)[E], uint32_t
         const uint32_t d = (uint32_t)(key[j] >> 32) - lo;
         b[j] = b[j] * slots + (mul ? __umulhi(d, mul) : d);
     }
+    return span != 0;
 }
 
 // Places the keys in L.stage by bucket (L.off, L.bucket follow; ends with a
-// barrier) and returns whether some bucket has more than kBucketRank keys. L.off
-// must not be in use by another wavefront when this is called.
+// barrier) and returns 0, 1 when some bucket has more than kBucketRank keys, or 2
+// when one has more than kBucketMost. L.off must not be in use by another
+// wavefront when this is called.
 template <int E, int NT, int CAP>
-__device__ __forceinline__ bool place_buckets(const uint64_t (&key)[E], const uint32_t (&b)[E], uint32_t n,
+__device__ __forceinline__ int place_buckets(const uint64_t (&key)[E], const uint32_t (&b)[E], uint32_t n,
                                               BucketLds<NT, CAP>& L) {
     constexpr int kPer = kBucketSlots / NT;
     for (int k = threadIdx.x; k < kBucketSlots; k += NT) L.off[k] = 0;
@@ -261,7 +268,34 @@ __device__ __forceinline__ bool place_buckets(const uint64_t (&key)[E], const ui
         L.stage[q] = key[j];
         L.bucket[q] = (uint16_t)b[j];
     }
-    return __syncthreads_or(longest > (uint32_t)kBucketRank) != 0;
+    if (__syncthreads_or(longest > (uint32_t)kBucketRank) == 0) return 0;
+    return __syncthreads_or(longest > (uint32_t)kBucketMost) == 0 ? 1 : 2;
+}
+
+// Orders the buckets of more than kBucketRank keys, up to kBucketMost, in the
+// stage; neighbouring buckets go to different wavefronts. Ends with a barrier.
+template <int NT, int CAP>
+__device__ __forceinline__ void sort_long_buckets(BucketLds<NT, CAP>& L) {
+    constexpr int NW = NT / kWave;
+    static_assert(kBucketMost <= 8 * kWave && kBucketSlots % NT == 0, "keys of a wavefront's network, whole rounds");
+    const RecordSink none{};
+    for (int k0 = 0; k0 < kBucketSlots; k0 += NT) {
+        const int k = k0 + lane() * NW + (int)threadIdx.x / kWave;
+        const uint32_t at = L.off[k], len = L.off[k + 1] - at;
+        uint64_t todo = ballot(len > (uint32_t)kBucketRank && len <= (uint32_t)kBucketMost);
+        while (todo) {
+            const int src = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            const uint32_t b = shfl_u32(at, src), n = shfl_u32(len, src);
+            if (n <= 2 * kWave)
+                sort_wave_reg<2, false>(L.stage + b, 0u, 0u, n, none);
+            else if (n <= 4 * kWave)
+                sort_wave_reg<4, false>(L.stage + b, 0u, 0u, n, none);
+            else
+                sort_wave_reg<8, false>(L.stage + b, 0u, 0u, n, none);
+        }
+    }
+    __syncthreads();
 }
 
 // Place of the key v within its bucket [b, b + len) of the stage: its rank
