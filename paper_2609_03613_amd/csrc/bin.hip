@@ -822,32 +822,36 @@ union LargeLds {
     PlaceLds place;
 };
 
-// One segment of 513..8192 keys by the workgroup, E keys per thread: above
-// kNetworkMost keys by bucket sort over the segment's own depth range, up to
-// it, or when a bucket holds more than kBucketMost keys, by the register / lane
-// / LDS bitonic network of sort_block_reg; coalesced loads and stores (with the
-// records when !DESC). The network makes 91 compare steps over 8192 keys, the
-// bucket sort a few LDS accesses per key: with a longest segment of 4295 keys
-// (10 million Gaussians on 1920x1080) this launch took 249 us, now 25.
-// Shorter segments are mostly those of the first and last bins, whose depths are
-// clustered: with buckets of up to 512 keys ordered by rank the launch took 38 us
-// for 500 thousand Gaussians in random order on 640x360, with a wavefront per
-// long bucket 16, with the network 8.5.
+// One segment of 513..8192 keys by the workgroup, E keys per thread: bucket
+// sort over the segment's own depth range, or the register / lane / LDS bitonic
+// network of sort_block_reg; coalesced loads and stores (with the records when
+// !DESC). Above kNetworkMost keys the network takes only what the bucket sort
+// cannot (a bucket of more than kBucketMost keys, or all of one depth): it makes
+// 91 compare steps over 8192 keys, the bucket sort a few LDS accesses per key
+// (a longest segment of 4295 keys, 10 million Gaussians on 1920x1080: 249 us for
+// this launch, now 25). Up to it the network also takes clustered segments, and
+// every one where there are few, no more than a workgroup each: those are mostly
+// of the first and last bins, whose depths are clustered (500 thousand Gaussians
+// in random order on 640x360: 38 us with buckets of up to 512 keys by rank, 16
+// with a wavefront per long bucket, 8.5 so). Where there are many, the bucket
+// sort halves the work (binning 8 million Gaussians on 3840x2160 without
+// sub-bins 1020 us, 1140 with the network).
 constexpr int kNetworkMost = 2048;
 template <int E, bool DESC>
 __device__ __forceinline__ void sort_large_block(uint64_t* pairs, uint32_t s, uint32_t begin, uint32_t len,
-                                                 const RecordSink& rs, LargeLds& lds) {
+                                                 const RecordSink& rs, bool few, LargeLds& lds) {
     constexpr uint32_t P = (uint32_t)kLargeThreads * E;
     uint64_t v[E];
-    if constexpr (E * kLargeThreads > kNetworkMost) {
+    constexpr bool kLong = E * kLargeThreads > kNetworkMost;
+    if (kLong || !few) {
         uint32_t b[E] = {};
 #pragma unroll
         for (int j = 0; j < E; ++j) v[j] = pairs[begin + min((uint32_t)(j * kLargeThreads) + threadIdx.x, len - 1)];
         BucketLds<kLargeThreads, kLargeCap>& L = lds.buckets;
         const bool apart = range_buckets(v, b, 1u, L);
         const int clustered = apart ? place_buckets(v, b, len, L) : 2;
-        if (clustered < 2) {
-            if (clustered) sort_long_buckets(L);
+        if (clustered < (kLong ? 2 : 1)) {
+            if (kLong && clustered) sort_long_buckets(L);
             for (uint32_t q = threadIdx.x; q < len; q += kLargeThreads) {
                 const uint32_t k = L.bucket[q], at = L.off[k], n = L.off[k + 1] - at;
                 const uint64_t x = L.stage[q];
@@ -880,15 +884,15 @@ __device__ __forceinline__ void sort_large_block(uint64_t* pairs, uint32_t s, ui
 
 template <bool DESC>
 __device__ __forceinline__ void sort_large(uint64_t* pairs, uint32_t s, uint32_t begin, uint32_t len,
-                                           const RecordSink& rs, LargeLds& lds) {
+                                           const RecordSink& rs, bool few, LargeLds& lds) {
     if (len <= 1024)
-        sort_large_block<2, DESC>(pairs, s, begin, len, rs, lds);
+        sort_large_block<2, DESC>(pairs, s, begin, len, rs, few, lds);
     else if (len <= 2048)
-        sort_large_block<4, DESC>(pairs, s, begin, len, rs, lds);
+        sort_large_block<4, DESC>(pairs, s, begin, len, rs, few, lds);
     else if (len <= 4096)
-        sort_large_block<8, DESC>(pairs, s, begin, len, rs, lds);
+        sort_large_block<8, DESC>(pairs, s, begin, len, rs, few, lds);
     else
-        sort_large_block<16, DESC>(pairs, s, begin, len, rs, lds);
+        sort_large_block<16, DESC>(pairs, s, begin, len, rs, few, lds);
 }
 
 // A segment of more than 8192 keys, in global memory.
@@ -940,6 +944,7 @@ __global__ void __launch_bounds__(kLargeThreads) sort_large_kernel(const uint32_
     __shared__ LargeLds lds;
     const uint32_t counts[3] = {bucket_count[5], bucket_count[6], bucket_count[7]};
     const bool off = stopped(to.stop);
+    const bool few = counts[0] + counts[1] <= gridDim.x;
     for (int bucket = 5; bucket <= 7; ++bucket) {
         for (uint32_t i = blockIdx.x; i < counts[bucket - 5]; i += gridDim.x) {
             const int64_t at = (int64_t)bucket * nseg + i;
@@ -947,7 +952,7 @@ __global__ void __launch_bounds__(kLargeThreads) sort_large_kernel(const uint32_
             locate<DESC>(bin_off, DESC ? reinterpret_cast<const uint2*>(lists)[at] : make_uint2(lists[at], 0u), s,
                          begin, len);
             if (bucket < 7)
-                sort_large<DESC>(pairs, s, begin, len, rs, lds);
+                sort_large<DESC>(pairs, s, begin, len, rs, few, lds);
             else
                 sort_global<DESC>(pairs, s, begin, len, rs);
         }

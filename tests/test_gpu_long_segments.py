@@ -1,7 +1,8 @@
 """Segments of 513..8192 pairs around the lengths and clusters where their sort
-changes: the network up to 2048 pairs and for more than 512 pairs of one depth
-bucket, else buckets ordered by rank (up to 64 pairs) or by a wavefront (up to
-512), with and without records, queued as segments and as sub-segments.
+changes: the network up to 2048 pairs where there are few such segments or they
+are clustered, and for more than 512 pairs of one depth bucket, else buckets
+ordered by rank (up to 64 pairs) or by a wavefront (up to 512), with and without
+records, queued as segments and as sub-segments.
 Bit-exact against the oracle's schedule."""
 import numpy as np
 import pytest
@@ -26,13 +27,13 @@ CLUSTERS = {
 }
 
 
-def segments(clusters, spread, seed):
+def segments(lengths, clusters, spread, seed):
     """One tile per length; the tile's depths uniform over its own range but for
     the clusters, each within `spread` of one depth."""
     rng = np.random.default_rng(seed)
     depth, tile = [], []
-    for t, n in enumerate(LENGTHS):
-        lo = 2.0 + t
+    for t, n in enumerate(lengths):
+        lo = 2.0 + t % 20
         z = rng.uniform(lo, lo + 0.5, n)
         if clusters is None:
             z[:] = lo
@@ -51,8 +52,21 @@ def segments(clusters, spread, seed):
 @pytest.mark.parametrize("spread", [0.0, 2e-6])
 @pytest.mark.parametrize("clusters", list(CLUSTERS))
 def test_long_segments(clusters, spread, packed, sub):
-    depth, tile = segments(CLUSTERS[clusters], spread, len(clusters))
-    n, tx = len(depth), len(LENGTHS)
+    check(LENGTHS, CLUSTERS[clusters], spread, packed, sub)
+
+
+@pytest.mark.parametrize("packed", [0, 1])
+@pytest.mark.parametrize("count", [256, 257, 600])
+@pytest.mark.parametrize("clusters", ["none", "ranks", "wavefronts", "a full bucket", "all equal"])
+def test_many_long_segments(clusters, count, packed):
+    # more of them than the launch has workgroups
+    lengths = [(513, 600, 1024, 1025, 1500, 2048)[k % 6] for k in range(count)]
+    check(lengths, CLUSTERS[clusters], 0.0, packed, 1)
+
+
+def check(lengths, clusters, spread, packed, sub):
+    depth, tile = segments(lengths, clusters, spread, len(clusters or ()))
+    n, tx = len(depth), len(lengths)
     rect = np.stack([tile, np.zeros(n, np.int64), tile + 1, np.ones(n, np.int64)], 1)
     ref = oracle.schedule(depth, rect, tx, 1, K=1, znear=0.01, zfar=1e10)
     dev = torch.device("cuda:0")
