@@ -531,7 +531,7 @@ __global__ void __launch_bounds__(kCountThreads) group_count_kernel(const uint4*
 constexpr int kScatterThreads = TGS_SCATTER_THREADS;  // threads of a group-scatter workgroup
 
 // TAG: the entry's tile within the group goes into the spare upper bits of its
-// id, and no code is written (kTagMin).
+// id, and no code is written (may_tag).
 template <bool VAR, bool TAG>
 __global__ void __launch_bounds__(kScatterThreads) group_scatter_kernel(const uint4* __restrict__ info, int64_t n,
                                                             const uint32_t* __restrict__ emit_off,

@@ -205,7 +205,7 @@ Layout layout(int64_t n, int64_t capacity, int64_t T, int K, int order, bool var
         size_t entry = sizeof(uint32_t);
         // groups are split with sub-bins (exact repair without records), when
         // the capacity allows groups that long
-        const bool split = L.gm.SB > 1 && capacity > (int64_t)kSplitMin && capacity > L.gm.G * kSplitMean;
+        const bool split = L.gm.SB > 1 && may_split(capacity, L.gm.G);
         if (L.gm.SB > 1) {
             // queued as {begin, length}, disjoint runs of two or more of the at
             // most capacity entries: sub-segments, each once, and in the parts of
@@ -590,7 +590,8 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
         // no codes for many entries, where the tile within the group fits above
         // the id and the bin follows from the sort key
         while (1 << gm.tag_bits < gm.GT) ++gm.tag_bits;
-        gm.tagged = cap > kTagMin && !var && !params->near_shift && n <= (int64_t)1 << (32 - gm.tag_bits);
+        gm.tagged = may_tag(cap, gm.G, L.sp.max_slices > 0) && !var && !params->near_shift &&
+                    n <= (int64_t)1 << (32 - gm.tag_bits);
         uint32_t* gcount = zero + L.gcount;
         uint32_t* group_off = (uint32_t*)(w + L.group_off);
         uint32_t* wgbase = (uint32_t*)(w + L.wgbase);

@@ -248,7 +248,7 @@ struct GroupMap {
     uint32_t GT_mul;  // ceil(2^32 / GT), or 0
     int chunk;        // Gaussians per workgroup of the group count and scatter
     int tag_bits;     // bits of a tile number within the group
-    bool tagged;      // the grouped pairs carry it above the id, and no codes are stored (kTagMin)
+    bool tagged;      // the grouped pairs carry it above the id, and no codes are stored (may_tag)
     int64_t T;
     const uint32_t* seg_base;
     const uint2* tile_seg;
@@ -272,7 +272,10 @@ constexpr int kMaxGroupSegs = 4096;   // LDS counters of one group sort
 // of 2 to count an entry, which where there are fewer entries costs the longest
 // group more than the scatter gains (a frame of one million on 1920x1080, 4
 // million of capacity: 355.5 us, 357.5 with tiles; the training step, 8.8
-// million: 699, 674 with tiles).
+// million: 699, 674 with tiles). The same where long groups are not split, unless
+// the entries are so many that no group stands out (may_tag; binning 2.5 million
+// on 1920x1080, 10 million of capacity: 210 us, 218 with tiles; 8 million on
+// 3840x2160 without sub-bins, 32 million: 1204, 1142 with tiles).
 constexpr int64_t kTagMin = 6 << 20;
 // Gaussians per workgroup of the group count / scatter: 2048, and fewer, down to
 // 256, while that makes fewer than kMinChunks workgroups, each a chain of slabs
@@ -315,10 +318,16 @@ GroupMap group_map_var(int64_t T, int K, int sub);
 // group is read and written once more, which pays where the group sort's
 // scattered stores and the queued sub-segments cost more than that (binning of
 // 10 million Gaussians 1050 us, 1060 at 8192 and 1072 at 32768; a 1297x840
-// training step 743, 765 and 755). kSplitMean: below 4096 entries of capacity
-// per group, groups that long are rare, and the extra launch and the larger one
-// that mostly find nothing cost 10 us (the frame of one million on 1920x1080,
-// 3922 per group: 397 us against 389).
+// training step 743, 765 and 755).
+// Whether any are is decided by the capacity per group (may_split). Up to
+// kSplitMean the longest groups are few and take no longer than the extra launch
+// and the larger one behind it, 20 us and more: binning on 1920x1080 at 4117,
+// 6274, 9803 and 15686 entries of capacity per group (1.05, 1.6, 2.5 and 4 million
+// Gaussians) takes 116, 157, 210 and 320 us whole, 134, 176, 225 and 310 split; on
+// 640x360 at 8695 and 17391 (250 and 500 thousand) 87 and 127, 97 and 109.
+// Above kMany entries of capacity the fixed costs no longer count and the
+// scattered stores of groups past the stage do: from kManyMean per group (the
+// stage) on (6 million on 3840x2160, 5925 per group: 720 whole, 666 split).
 constexpr int kSlice = 4096;       // entries per slice workgroup
 constexpr int kPartStep = 3072;    // entries between part boundaries
 constexpr int kPartCode = 1024;    // a code of more entries is a part by itself
@@ -330,7 +339,18 @@ constexpr int kMaxParts = kMaxGroupSegs;
 // part is queued for the long-segment sort.
 constexpr int kBucketMost = 512;
 constexpr uint32_t kSplitMin = 16384;
-constexpr int64_t kSplitMean = 4096;
+constexpr int64_t kSplitMean = 12288;
+constexpr int64_t kMany = 16 << 20;
+constexpr int64_t kManyMean = 4096;
+// Groups can be split (with sub-bins).
+inline bool may_split(int64_t capacity, int G) {
+    return capacity > (int64_t)kSplitMin &&
+           (capacity > G * kSplitMean || (capacity > kMany && capacity > G * kManyMean));
+}
+// The grouped pairs can carry their tile.
+inline bool may_tag(int64_t capacity, int G, bool split) {
+    return capacity > kTagMin && (split || capacity > kMany || capacity <= G * kManyMean);
+}
 __host__ __device__ __forceinline__ bool split_group(uint32_t n) { return n > kSplitMin; }
 struct GroupSplit {
     uint4* list;      // slices {group, split index, begin, end}; null: no split groups
