@@ -34,10 +34,10 @@
 // Bound by VALU issue. Summing the nine gradients of every entry over the
 // wavefront (33 instructions of recursive halving, after 17 to form them)
 // took 233 us on 500k Gaussians at 1297x840 with 32-pixel tiles; the batches
-// take 198 us. The same contraction on the matrix cores (16 binary32 16x16x4
-// products per batch, the monomials as the constant operand) took 226 us: a
-// binary32 product occupies its SIMD for 33 cycles and no vector
-// instruction of another wavefront is issued meanwhile.
+// take 188 us (198 with four workgroups per CU, see BwdLds). The same contraction
+// on the matrix cores (16 binary32 16x16x4 products per batch, the monomials as
+// the constant operand) took 226 us: a binary32 product occupies its SIMD for 33
+// cycles and no vector instruction of another wavefront is issued meanwhile.
 #include <math.h>
 
 #include "raster.hpp"
@@ -58,17 +58,29 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBatch = 8;     // entries per batch
 constexpr int kWords = 9;     // gradient words per entry
-constexpr int kRowLen = 68;   // row stride in LDS words: 16-byte reads of 8 rows hit distinct banks
 constexpr int kSumLen = 12;   // LDS words per entry of the summed gradient words
 
-// Per-wavefront LDS of the backward walk.
-struct BwdLds {
+// Per-wavefront LDS of the backward walk. At 31744 bytes a workgroup of four
+// wavefronts, and under 96 registers, a CU holds five workgroups (LDS is given
+// out in pieces of 1280 bytes); with rows padded to 68 words (8288 bytes a
+// wavefront) and 106 registers it held four, and blocks of a few entries, which
+// are chains of memory latencies, waited for a place: 6 thousand Gaussians on
+// 1281x1041 47.6 us, now 42; 500 thousand on 1297x840 with 32-pixel tiles 199,
+// now 188. The bank conflicts of the unpadded rows cost nothing measurable.
+struct __align__(16) BwdLds {
     union {
-        float row[2 * kBatch * kRowLen];  // d of the batch's entries, then w; [entry][pixel]
-        float sum[kBatch * kSumLen];      // after the row sums: the batch's gradient words
+        Staged stage[kWave + 2];  // the last two are read ahead, never written
+        struct {
+            Staged slots[kWave];
+            union {
+                float row[2 * kBatch * kWave];  // d of the batch's entries, then w; [entry][pixel]
+                float sum[kBatch * kSumLen];    // after the row sums: the batch's gradient words
+            };
+            float g[3][kWave];  // upstream colour gradients of the block's pixels
+        };
     };
-    float g[3][kWave];  // upstream colour gradients of the block's pixels
 };
+static_assert((4 * sizeof(BwdLds) + 1279) / 1280 * 5 <= 160 * 1024 / 1280, "five workgroups per CU");
 
 // Sums of a over the lane pairs (l, l ^ 32) in the lower half and of b in the
 // upper half.
@@ -91,21 +103,19 @@ __device__ __forceinline__ float sum8(float v) {
 // LDS of four, only four such wavefronts fit a CU: 200 thousand Gaussians on
 // 1200x800 took 414 us, now 155), else 4.
 template <int SRC, int NW>
-__global__ void __launch_bounds__(NW * kWave) raster_bwd_kernel(RasterArgs A, const float* __restrict__ d_rgb,
+__global__ void __launch_bounds__(NW * kWave, 5) raster_bwd_kernel(RasterArgs A, const float* __restrict__ d_rgb,
                                                          const float* __restrict__ d_alpha,
                                                          const float* __restrict__ trans_in,
                                                          const int32_t* __restrict__ last_in,
                                                          float* __restrict__ d_splats) {
 #pragma clang fp contract(off)
-    __shared__ Staged stage[NW][kWave + 2];
-    __shared__ __align__(16) BwdLds lds[NW];
+    __shared__ BwdLds lds[NW];
     const int w = threadIdx.x / kWave, l = lane();
     WaveBlock wb;
     if (!block_of_wave(A, w, wb)) return;
     const int x0 = wb.tx * A.tile, y0 = wb.ty * A.tile;
     float xa, xb, ya, yb;
     if (!block_box_at(wb.bx, wb.by, x0, y0, A.width, A.height, xa, xb, ya, yb)) return;  // block outside the image
-    if (A.counters[2] != 0) return;  // truncated stream: the forward image is NaN, no gradient
     const int lx = wb.bx + (l & 7), ly = wb.by + (l >> 3);
     const int x = x0 + lx, y = y0 + ly;
     const bool inside = x < A.width && y < A.height;
@@ -113,31 +123,47 @@ __global__ void __launch_bounds__(NW * kWave) raster_bwd_kernel(RasterArgs A, co
     const float px = (float)lx + 0.5f, py = (float)ly + 0.5f;
     const uint32_t begin = tile_begin(A, wb.t);
     const uint32_t end = tile_end(A, wb.t);
-    Staged* st = stage[w];
+    Staged* st = lds[w].stage;
 
-    // pass 1: the forward walk, or the forward's saved T and last
+    // pass 1: the forward walk, or the forward's saved T and last (requested
+    // before the flag is waited for, and the ids below before the upstream
+    // gradients: 6 thousand Gaussians on 1281x1041 47.6 us, 45 so)
+    const int64_t pixel = (int64_t)y * A.width + x;
     Pix p{1.0f, 0.f, 0.f, 0.f, -1, 0, 0, 0, !inside};
-    if (trans_in) {
-        if (inside) {
-            const int64_t i = (int64_t)y * A.width + x;
-            p.T = trans_in[i];
-            p.last = last_in[i];
-        }
-    } else {
-        wave_forward<SRC, false>(A, st, wb.bi, begin, end, ox, oy, px, py, xa, xb, ya, yb, p);
+    if (trans_in && inside) {
+        p.T = trans_in[pixel];
+        p.last = last_in[pixel];
     }
+    if (A.counters[2] != 0) return;  // truncated stream: the forward image is NaN, no gradient
+    if (!trans_in) wave_forward<SRC, false>(A, st, wb.bi, begin, end, ox, oy, px, py, xa, xb, ya, yb, p);
 
     // pass 2: backwards from the last composited entry
     const int hi = wave_max_i32(p.last);
     if (hi < 0) return;
+    // Chunks of 64 entries downwards from hi; lane l holds entry top - l. The
+    // gathers are software-pipelined as in the forward walk: while chunk i
+    // is processed, the splats of chunk i + 1 are in flight and the ids of
+    // chunk i + 2 follow once chunk i's ids are staged. Every lane issues
+    // every load (lanes below the range read its first entry and are
+    // dropped by the range test).
+    const float4* sp = reinterpret_cast<const float4*>(A.splats);
+    auto id_clamped = [&](int64_t e) { return id_at<SRC>(A, (uint32_t)(e >= (int64_t)begin ? e : (int64_t)begin)); };
+    auto gather = [&](uint32_t g, float4& r0, float4& r1, float4& r2) {
+        const float4* q = sp + kSplatVec * (int64_t)g;
+        r0 = q[0];
+        r1 = q[1];
+        r2 = q[2];
+    };
+    float4 a0, a1, a2, b0, b1, b2;
+    uint32_t ida = id_clamped((int64_t)hi - l), idb = id_clamped((int64_t)hi - kWave - l);
     float gr = 0.f, gg = 0.f, gb = 0.f, ga = 0.f;
     if (inside) {
-        const int64_t i = (int64_t)y * A.width + x;
-        gr = d_rgb[3 * i];
-        gg = d_rgb[3 * i + 1];
-        gb = d_rgb[3 * i + 2];
-        ga = d_alpha ? d_alpha[i] : 0.f;
+        gr = d_rgb[3 * pixel];
+        gg = d_rgb[3 * pixel + 1];
+        gb = d_rgb[3 * pixel + 2];
+        ga = d_alpha ? d_alpha[pixel] : 0.f;
     }
+    gather(ida, a0, a1, a2);
     const float Tf = p.T;
     float T = Tf;
     float R = Tf * (gr * A.bg[0] + gg * A.bg[1] + gb * A.bg[2] - ga);
@@ -150,7 +176,6 @@ __global__ void __launch_bounds__(NW * kWave) raster_bwd_kernel(RasterArgs A, co
     L.g[0][l] = odd ? 0.f : gr;
     L.g[1][l] = odd ? 0.f : gg;
     L.g[2][l] = odd ? 0.f : gb;
-    const float4* sp = reinterpret_cast<const float4*>(A.splats);
     const float cx = (float)wb.bx + 4.0f, cy = (float)wb.by + 4.0f;  // block centre, tile-local
     // the transposed role of this lane: entry l % 8 of the batch, pixel row l / 8
     const int te = l & 7, ty = l >> 3;
@@ -176,8 +201,8 @@ __global__ void __launch_bounds__(NW * kWave) raster_bwd_kernel(RasterArgs A, co
         float wd[6], cr, cg, cb;
         {
 #pragma clang fp contract(fast)
-            const f32x4* dp = reinterpret_cast<const f32x4*>(L.row + te * kRowLen + 8 * ty);
-            const f32x4* wp = reinterpret_cast<const f32x4*>(L.row + (kBatch + te) * kRowLen + 8 * ty);
+            const f32x4* dp = reinterpret_cast<const f32x4*>(L.row + te * kWave + 8 * ty);
+            const f32x4* wp = reinterpret_cast<const f32x4*>(L.row + (kBatch + te) * kWave + 8 * ty);
             const f32x4 d0 = dp[0], d1 = dp[1], v0 = wp[0], v1 = wp[1];
             // dx = u - X and dy = v with (u, v) the mean's offset from the
             // block centre and from the row, from the staged mean: the d are
@@ -238,19 +263,6 @@ __global__ void __launch_bounds__(NW * kWave) raster_bwd_kernel(RasterArgs A, co
         nb = 0;
         wave_sync();
     };
-    // Chunks of 64 entries downwards from hi; lane l holds entry top - l. The
-    // gathers are software-pipelined as in the forward walk: while chunk i
-    // is processed, the splats of chunk i + 1 are in flight and the ids of
-    // chunk i + 2 follow once chunk i's ids are staged. Every lane issues
-    // every load (lanes below the range read its first entry and are
-    // dropped by the range test).
-    auto id_clamped = [&](int64_t e) { return id_at<SRC>(A, (uint32_t)(e >= (int64_t)begin ? e : (int64_t)begin)); };
-    auto gather = [&](uint32_t g, float4& r0, float4& r1, float4& r2) {
-        const float4* q = sp + kSplatVec * (int64_t)g;
-        r0 = q[0];
-        r1 = q[1];
-        r2 = q[2];
-    };
     auto chunk = [&](int64_t top, const float4& q0, const float4& q1, const float4& q2, uint32_t& gcur,
                      uint32_t g_next, float4& n0, float4& n1, float4& n2) {
         const int64_t e = top - l;
@@ -296,8 +308,8 @@ __global__ void __launch_bounds__(NW * kWave) raster_bwd_kernel(RasterArgs A, co
                 const float wt = alpha * Tk;
                 const float gc = gr * c.b.z + gg * c.b.w + gb * c.c.x;
                 const float dLda = Tk * gc - inv * R;
-                L.row[nb * kRowLen + l] = comp && araw <= kAlphaMax ? dLda * araw : 0.f;
-                L.row[(kBatch + nb) * kRowLen + l] = comp ? wt : 0.f;
+                L.row[nb * kWave + l] = comp && araw <= kAlphaMax ? dLda * araw : 0.f;
+                L.row[(kBatch + nb) * kWave + l] = comp ? wt : 0.f;
                 R = comp ? R + wt * gc : R;
                 T = comp ? Tk : T;
                 const uint32_t id = __float_as_uint(c.c.y);
@@ -320,16 +332,15 @@ __global__ void __launch_bounds__(NW * kWave) raster_bwd_kernel(RasterArgs A, co
             step(ca);
             ca = nx[2];
             if (left != 0) step(cb);
-            if (nb >= kBatch - 1) flush();
+            if (nb >= kBatch - 1) {
+                flush();
+                ca = nx[2];  // (not kept in registers meanwhile)
+            }
             if (left == 0) break;
             nx += 2;
         }
         wave_sync();
     };
-    float4 a0, a1, a2, b0, b1, b2;
-    uint32_t ida = id_clamped((int64_t)hi - l), idb;
-    gather(ida, a0, a1, a2);
-    idb = id_clamped((int64_t)hi - kWave - l);
     for (int64_t top = hi;;) {
         if (top < (int64_t)begin) break;
         chunk(top, a0, a1, a2, ida, idb, b0, b1, b2);
