@@ -245,7 +245,7 @@ def batched(args):
     """16 cameras of uneven resolution on a ring around 3M Gaussians (SH0):
     per-view tile size and bins from the autotuner, the whole multi-view
     frame (projection in launches of eight views, 16 binnings on four
-    streams, one persistent raster launch) captured in a HIP graph and
+    streams, one raster launch) captured in a HIP graph and
     replayed. Beside it: the same frame launched eagerly, eagerly with the
     binnings on one stream, and the per-view default path (16 px tiles,
     K = 64, one raster launch per view)."""
@@ -307,7 +307,7 @@ def batched(args):
 
     default_ms = timed(per_view, args.steps)
     # the tuned tile sizes and bins, still one raster launch per view: the
-    # tuning's share of the gain, apart from the single persistent launch
+    # tuning's share of the gain, apart from the single raster launch
     tviews = [tg.Renderer(c, p, device=dev) for c, p in zip(cams, tuned)]
     tprep = []
     for r in tviews:

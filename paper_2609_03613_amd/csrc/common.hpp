@@ -279,10 +279,11 @@ constexpr int kMaxGroupSegs = 4096;   // LDS counters of one group sort
 constexpr int64_t kTagMin = 6 << 20;
 // Gaussians per workgroup of the group count / scatter: 2048, and fewer, down to
 // 256, while that makes fewer than kMinChunks workgroups, each a chain of slabs
-// one after the other (binning 20 thousand Gaussians 62.6 us with 2048, now 57.9;
-// 100 thousand 68.0, now 63.4). More workgroups than that cost more than they
-// shorten, in the group count's additions to the same words: a 1297x840 training
-// step of 500 thousand Gaussians 696 us with 2048, 705 with 1024, 712 with 512.
+// one after the other (binning on 1920x1080 in random order: 20 thousand Gaussians
+// 60.8 us with 2048, now 55.4; 100 thousand 66.8, now 61.5). More workgroups than
+// that cost more than they shorten, in the group count's additions to the same
+// words: a 1297x840 training step of 500 thousand Gaussians 668 us with 2048, 674
+// with 1024, 681 with 512.
 constexpr int kMinChunks = 128;
 inline int group_chunk(int64_t n) {
     int c = 2048;
@@ -310,15 +311,15 @@ GroupMap group_map_var(int64_t T, int K, int sub);
 // entries is split over the chip, by slices of kSlice entries that are ordered
 // by part first; a part is a run of codes with less than kPartStep + kPartCode
 // entries, or one code (3072 and 1024 rather than 2048 and 2048: the parts are
-// fuller, the captured batch of 16 views 9870 us instead of 10407, binning 10
-// million Gaussians 893 instead of 912; 3328 and 768: 9775 and 893). One workgroup per group took as long as its longest group: 112 us
-// of group sort on 640x360 with one million Gaussians (now 23, and 20 for the
-// split), 398 us on 1920x1080 with 10 million (now 87 and 143), with 249 us for
-// the longest sub-segment behind it (now 36). The line at 16384 entries: a split
+// fuller, the captured batch of 16 views 9840 us instead of 10380, binning 10
+// million Gaussians 864 instead of 882; 3328 and 768: 9780 and 867). One
+// workgroup per group took as long as its longest group: 112 us of group sort on
+// 640x360 with one million Gaussians (now 22, and 21 for the split), 398 us on 1920x1080 with 10 million (now 86 and 141), with 249 us for
+// the longest sub-segment behind it (now 25). The line at 16384 entries: a split
 // group is read and written once more, which pays where the group sort's
 // scattered stores and the queued sub-segments cost more than that (binning of
-// 10 million Gaussians 1050 us, 1060 at 8192 and 1072 at 32768; a 1297x840
-// training step 743, 765 and 755).
+// 10 million Gaussians 864 us, 879 at 8192 and 873 at 32768; a 1297x840 training
+// step 668, 679 and 681).
 // Whether any are is decided by the capacity per group (may_split). Up to
 // kSplitMean the longest groups are few and take no longer than the extra launch
 // and the larger one behind it, 20 us and more: binning on 1920x1080 at 4117,
@@ -333,7 +334,7 @@ constexpr int kPartStep = 3072;    // entries between part boundaries
 constexpr int kPartCode = 1024;    // a code of more entries is a part by itself
 // LDS counters of a slice workgroup, enough for a part per code: no group is too
 // long (5 million Gaussians on 280x207, three groups of 1.4 million entries, with
-// room for 2048 parts, hence groups of at most 0.9 million: 1980 us, now 795)
+// room for 2048 parts, hence groups of at most 0.9 million: 1980 us, now 786)
 constexpr int kMaxParts = kMaxGroupSegs;
 // Longest bucket that a workgroup bucket sort orders itself; a longer one of a
 // part is queued for the long-segment sort.

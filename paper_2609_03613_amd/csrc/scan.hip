@@ -765,7 +765,7 @@ constexpr int kSortBatch = TGS_SORT_BATCH;      // entries per thread and sweep 
 // descriptors (SB > 1: exact repair, no records) and the group has at most
 // kStage entries: they are placed at their code offsets in LDS, each
 // sub-segment of 2..kRankMax entries is put in pair order there (an entry's
-// rank among its sub-segment's pairs, ties by slot), and the group is
+// rank among its sub-segment's pairs), and the group is
 // written out in order: the output is written in runs instead of one
 // scattered 8-byte store per entry, and the short sub-segments need no
 // repair pass.
