@@ -756,7 +756,7 @@ __device__ __forceinline__ void sort_parts(uint64_t* __restrict__ pairs, const u
         const bool room = P.nlong + (uint32_t)(kPartCap / (kBucketRank + 1)) <= (uint32_t)kLongMost;
         const uint32_t rank_most = room ? kBucketRank : kBucketMost;
         range_buckets(pr, b, u.w, L);
-        const int clustered = place_buckets(pr, b, n, L);
+        const bool clustered = place_buckets<0u>(pr, b, n, L) != 0;
         load(it + gridDim.x);
         for (uint32_t q = threadIdx.x; q < n; q += NT) {
             const uint32_t k = L.bucket[q], at = L.off[k], len = L.off[k + 1] - at;
@@ -825,32 +825,32 @@ union LargeLds {
 // One segment of 513..8192 keys by the workgroup, E keys per thread: bucket
 // sort over the segment's own depth range, or the register / lane / LDS bitonic
 // network of sort_block_reg; coalesced loads and stores (with the records when
-// !DESC). Above kNetworkMost keys the network takes only what the bucket sort
-// cannot (a bucket of more than kBucketMost keys, or all of one depth): it makes
-// 91 compare steps over 8192 keys, the bucket sort a few LDS accesses per key
-// (a longest segment of 4295 keys, 10 million Gaussians on 1920x1080: 249 us for
-// this launch, now 25). Up to it the network also takes clustered segments, and
-// every one where there are few, no more than a workgroup each: those are mostly
-// of the first and last bins, whose depths are clustered (500 thousand Gaussians
-// in random order on 640x360: 38 us with buckets of up to 512 keys by rank, 16
-// with a wavefront per long bucket, 8.5 so). Where there are many, the bucket
-// sort halves the work (binning 8 million Gaussians on 3840x2160 without
-// sub-bins 1020 us, 1140 with the network).
+// !DESC). The network makes 91 compare steps over 8192 keys, the bucket sort a
+// few LDS accesses per key (a longest segment of 4295 keys, 10 million Gaussians
+// on 1920x1080: 249 us for this launch, now 25). The segments of the first and
+// last bins are clustered: a bucket of more than kBucketRank keys sends a segment
+// of up to kNetworkMost keys to the network, before anything is placed (500
+// thousand Gaussians in random order on 640x360: 38 us with buckets of up to 512
+// keys by rank, 16 with a wavefront per long bucket, 11 so; 8.8 with the network
+// for all, which takes 12 instead of 7.4 us where they are not clustered, 100
+// thousand on 640x360 with 16 whole bins). In a longer one wavefronts sort the
+// long buckets, up to kBucketMost keys, and the network takes what is left.
 constexpr int kNetworkMost = 2048;
 template <int E, bool DESC>
 __device__ __forceinline__ void sort_large_block(uint64_t* pairs, uint32_t s, uint32_t begin, uint32_t len,
-                                                 const RecordSink& rs, bool few, LargeLds& lds) {
+                                                 const RecordSink& rs, LargeLds& lds) {
     constexpr uint32_t P = (uint32_t)kLargeThreads * E;
-    uint64_t v[E];
     constexpr bool kLong = E * kLargeThreads > kNetworkMost;
-    if (kLong || !few) {
+    uint64_t v[E];
+    {
         uint32_t b[E] = {};
 #pragma unroll
         for (int j = 0; j < E; ++j) v[j] = pairs[begin + min((uint32_t)(j * kLargeThreads) + threadIdx.x, len - 1)];
         BucketLds<kLargeThreads, kLargeCap>& L = lds.buckets;
         const bool apart = range_buckets(v, b, 1u, L);
-        const int clustered = apart ? place_buckets(v, b, len, L) : 2;
-        if (clustered < (kLong ? 2 : 1)) {
+        constexpr uint32_t kMost = kLong ? kBucketMost : kBucketRank;
+        const int clustered = apart ? place_buckets<kMost>(v, b, len, L) : 2;
+        if (clustered < 2) {
             if (kLong && clustered) sort_long_buckets(L);
             for (uint32_t q = threadIdx.x; q < len; q += kLargeThreads) {
                 const uint32_t k = L.bucket[q], at = L.off[k], n = L.off[k + 1] - at;
@@ -884,15 +884,15 @@ __device__ __forceinline__ void sort_large_block(uint64_t* pairs, uint32_t s, ui
 
 template <bool DESC>
 __device__ __forceinline__ void sort_large(uint64_t* pairs, uint32_t s, uint32_t begin, uint32_t len,
-                                           const RecordSink& rs, bool few, LargeLds& lds) {
+                                           const RecordSink& rs, LargeLds& lds) {
     if (len <= 1024)
-        sort_large_block<2, DESC>(pairs, s, begin, len, rs, few, lds);
+        sort_large_block<2, DESC>(pairs, s, begin, len, rs, lds);
     else if (len <= 2048)
-        sort_large_block<4, DESC>(pairs, s, begin, len, rs, few, lds);
+        sort_large_block<4, DESC>(pairs, s, begin, len, rs, lds);
     else if (len <= 4096)
-        sort_large_block<8, DESC>(pairs, s, begin, len, rs, few, lds);
+        sort_large_block<8, DESC>(pairs, s, begin, len, rs, lds);
     else
-        sort_large_block<16, DESC>(pairs, s, begin, len, rs, few, lds);
+        sort_large_block<16, DESC>(pairs, s, begin, len, rs, lds);
 }
 
 // A segment of more than 8192 keys, in global memory.
@@ -944,7 +944,6 @@ __global__ void __launch_bounds__(kLargeThreads) sort_large_kernel(const uint32_
     __shared__ LargeLds lds;
     const uint32_t counts[3] = {bucket_count[5], bucket_count[6], bucket_count[7]};
     const bool off = stopped(to.stop);
-    const bool few = counts[0] + counts[1] <= gridDim.x;
     for (int bucket = 5; bucket <= 7; ++bucket) {
         for (uint32_t i = blockIdx.x; i < counts[bucket - 5]; i += gridDim.x) {
             const int64_t at = (int64_t)bucket * nseg + i;
@@ -952,7 +951,7 @@ __global__ void __launch_bounds__(kLargeThreads) sort_large_kernel(const uint32_
             locate<DESC>(bin_off, DESC ? reinterpret_cast<const uint2*>(lists)[at] : make_uint2(lists[at], 0u), s,
                          begin, len);
             if (bucket < 7)
-                sort_large<DESC>(pairs, s, begin, len, rs, few, lds);
+                sort_large<DESC>(pairs, s, begin, len, rs, lds);
             else
                 sort_global<DESC>(pairs, s, begin, len, rs);
         }

@@ -227,12 +227,12 @@ __device__ __forceinline__ bool range_buckets(const uint64_t (&key)[E], uint32_t
 }
 
 // Places the keys in L.stage by bucket (L.off, L.bucket follow; ends with a
-// barrier) and returns 0, 1 when some bucket has more than kBucketRank keys, or 2
-// when one has more than kBucketMost. L.off must not be in use by another
-// wavefront when this is called.
-template <int E, int NT, int CAP>
+// barrier) and returns 0, or 1 when some bucket has more than kBucketRank keys.
+// With MOST > 0 and a bucket of more than that, nothing is placed and 2 is
+// returned. L.off must not be in use by another wavefront when this is called.
+template <uint32_t MOST, int E, int NT, int CAP>
 __device__ __forceinline__ int place_buckets(const uint64_t (&key)[E], const uint32_t (&b)[E], uint32_t n,
-                                              BucketLds<NT, CAP>& L) {
+                                             BucketLds<NT, CAP>& L) {
     constexpr int kPer = kBucketSlots / NT;
     for (int k = threadIdx.x; k < kBucketSlots; k += NT) L.off[k] = 0;
     __syncthreads();
@@ -250,7 +250,10 @@ __device__ __forceinline__ int place_buckets(const uint64_t (&key)[E], const uin
     }
     const uint32_t incl = wave_inclusive_sum(s);
     if (lane() == kWave - 1) L.sum[threadIdx.x / kWave] = incl;
-    __syncthreads();
+    if (MOST == 0)
+        __syncthreads();
+    else if (__syncthreads_or(longest > MOST))
+        return 2;
     uint32_t run = incl - s;
 #pragma unroll
     for (int i = 0; i < NT / kWave; ++i) run += i < (int)(threadIdx.x / kWave) ? L.sum[i] : 0u;
@@ -268,8 +271,7 @@ __device__ __forceinline__ int place_buckets(const uint64_t (&key)[E], const uin
         L.stage[q] = key[j];
         L.bucket[q] = (uint16_t)b[j];
     }
-    if (__syncthreads_or(longest > (uint32_t)kBucketRank) == 0) return 0;
-    return __syncthreads_or(longest > (uint32_t)kBucketMost) == 0 ? 1 : 2;
+    return __syncthreads_or(longest > (uint32_t)kBucketRank) ? 1 : 0;
 }
 
 // Orders the buckets of more than kBucketRank keys, up to kBucketMost, in the

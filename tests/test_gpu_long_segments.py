@@ -1,8 +1,7 @@
 """Segments of 513..8192 pairs around the lengths and clusters where their sort
-changes: the network up to 2048 pairs where there are few such segments or they
-are clustered, and for more than 512 pairs of one depth bucket, else buckets
-ordered by rank (up to 64 pairs) or by a wavefront (up to 512), with and without
-records, queued as segments and as sub-segments.
+changes: buckets ordered by rank (up to 64 pairs) or, past 2048 pairs, by a
+wavefront (up to 512), else the network, with and without records, queued as
+segments and as sub-segments, fewer and more of them than workgroups.
 Bit-exact against the oracle's schedule."""
 import numpy as np
 import pytest
