@@ -103,11 +103,11 @@ __device__ __forceinline__ void depth_range_block(const uint4* __restrict__ info
                                                   float* __restrict__ zrange, const uint32_t* __restrict__ samples,
                                                   const int64_t* __restrict__ stop, RangeLds& R) {
 #pragma clang fp contract(off)
-    const int64_t V = counters[1];
-    if (stopped(stop)) return;
+    const int64_t V = counters[1], over = counters[2];
     const int n = (int)(V < S ? V : S);
+    const bool write = threadIdx.x == 0 && !(stop && over);
     if (n == 0) {
-        if (threadIdx.x == 0) {
+        if (write) {
             zrange[0] = znear;
             zrange[1] = zfar;
         }
@@ -197,7 +197,7 @@ __device__ __forceinline__ void depth_range_block(const uint4* __restrict__ info
         resolve(1, eb, b0, b1, r1);
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
+    if (write) {
         const float zlo = __uint_as_float(R.sel[0][0] + kmin);
         const float zhi = __uint_as_float(R.sel[1][0] + kmin);
         const float diff = zhi - zlo;
@@ -943,7 +943,7 @@ __global__ void __launch_bounds__(kLargeThreads) sort_large_kernel(const uint32_
                                                                    RepairSum sum) {
     __shared__ LargeLds lds;
     const uint32_t counts[3] = {bucket_count[5], bucket_count[6], bucket_count[7]};
-    const bool off = stopped(to.stop);
+    const bool off = bucket_count[kBuckets] != 0;  // (one request with the counts)
     for (int bucket = 5; bucket <= 7; ++bucket) {
         for (uint32_t i = blockIdx.x; i < counts[bucket - 5]; i += gridDim.x) {
             const int64_t at = (int64_t)bucket * nseg + i;

@@ -126,7 +126,7 @@ constexpr int kTicketSegs = 2;
 constexpr int kTicketSel = 3;
 constexpr int kSelCtl = 4;  // 2 words: first rejected segment + 1, remaining budget
 constexpr int kSplitCtl = 8;  // 3 words: split groups, slices, parts
-constexpr int kBucketCount = 16;
+constexpr int kBucketCount = 16;  // kBuckets words, then whether the call is stopped
 constexpr int kTileHist = 32;  // 66 words: histogram and cursors of the tile order
 constexpr int kControlWords = 128;
 
@@ -609,7 +609,7 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
             sp.hist = (uint32_t*)(w + L.split_hist);
             sp.ctl = zero + kSplitCtl;
         }
-        TGS_HIP(launch_group_scan(gcount, gm, out->counters_dev, group_off, group_order, cap, sp, s), "group scan");
+        TGS_HIP(launch_group_scan(gcount, gm, out->counters_dev, group_off, group_order, cap, sp, stop, bucket_count, s), "group scan");
         TGS_HIP(launch_group_scatter(pr->info_dev, n, emit_off, out->zrange_dev, nk, gm, tiles_x, tiles_y, group_off,
                                      wgbase, tmp_pair, tmp_code, cap, sp, stop, s),
                 "group scatter");
@@ -625,7 +625,7 @@ tgs_status tgs_bin(const tgs_projected* pr, const tgs_camera* cam, const tgs_par
         const RepairSum sum{all ? queued : nullptr, gm.G, out->counters_dev};
         TGS_HIP(launch_group_sort(tmp_pair, tmp_code, group_off, group_order, out->zrange_dev, gm, nseg, cap, out->pairs_dev,
                                   out->offsets_dev, seg_lists, L.list_stride, bucket_count, out->counters_dev, all,
-                                  out->repaired_dev, rs, queued, tile_count, sp, (uint16_t*)(w + L.part_tile), stop, s),
+                                  out->repaired_dev, rs, queued, tile_count, sp, (uint16_t*)(w + L.part_tile), s),
                 "group sort");
         if (rules)
             TGS_HIP(launch_repair_select(out->offsets_dev, T, K, params->repair_budget, zero + kTicketSel,

@@ -514,7 +514,8 @@ hipError_t launch_bin_scatter(const uint32_t* info, int64_t n, const uint32_t* e
 // wgbase [ceil(n / gm.chunk) x G] receives each workgroup's slice base
 // in the groups it touches. group_scan: group_off [G + 1] = exclusive
 // prefix of gcount (all zero when the entry count counters[0] does not fit 32
-// bits). group_scatter: tmp_pair / tmp_code [capacity] get every
+// bits), and when the call is stopped order [G] = -1 and the word behind the
+// kBuckets bucket counts set. group_scatter: tmp_pair / tmp_code [capacity] get every
 // entry (pair, segment within its group; no codes with gm.tagged) grouped by
 // group; positions past the capacity are dropped; order [G] = the groups, longest first.
 // group_sort: pairs in (tile, bin) order, bin_off
@@ -535,7 +536,8 @@ hipError_t launch_bin_scatter(const uint32_t* info, int64_t n, const uint32_t* e
 hipError_t launch_group_count(const uint32_t* info, int64_t n, const uint32_t* emit_off, GroupMap gm, int tiles_x,
                               int tiles_y, uint32_t* gcount, uint32_t* wgbase, const RangeArgs& ra, hipStream_t s);
 hipError_t launch_group_scan(const uint32_t* gcount, GroupMap gm, const int64_t* counters, uint32_t* group_off,
-                             uint32_t* order, int64_t capacity, const GroupSplit& sp, hipStream_t s);
+                             uint32_t* order, int64_t capacity, const GroupSplit& sp, const int64_t* stop,
+                             uint32_t* bucket_count, hipStream_t s);
 hipError_t launch_group_scatter(const uint32_t* info, int64_t n, const uint32_t* emit_off, const float* zrange,
                                 NearKey nk, GroupMap gm, int tiles_x, int tiles_y, const uint32_t* group_off,
                                 const uint32_t* wgbase, uint64_t* tmp_pair, uint16_t* tmp_code, int64_t capacity,
@@ -545,7 +547,7 @@ hipError_t launch_group_sort(const uint64_t* tmp_pair, uint16_t* tmp_code, const
                              uint32_t* lists, int64_t list_stride, uint32_t* bucket_count,
                              const int64_t* counters, bool queue_all, uint8_t* repaired, RecordSink rs,
                              uint32_t* queued, uint32_t* tile_count, const GroupSplit& sp, uint16_t* part_tile,
-                             const int64_t* stop, hipStream_t s);
+                             hipStream_t s);
 
 // Per-tile bin counts: seg_base[t] = exclusive prefix sum of the bin counts
 // (each clamped to 1..kmax and rounded down to a power of two), seg_base[T]

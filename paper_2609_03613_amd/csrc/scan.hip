@@ -642,7 +642,9 @@ __global__ void __launch_bounds__(kThreads) seg_base_kernel(const int32_t* __res
 // inside a class), so that the group sort starts the longest groups first.
 // A count of 2^32 entries or more wraps the prefix sums, and a position can then
 // belong to two groups: every group is empty instead (the stream is flagged as
-// truncated).
+// truncated). Where the call is stopped (see stopped()), the later launches learn
+// it from the words that they read first anyway: order[] = -1, and the word
+// behind the bucket counts is set.
 // With sp.list, also the slices of kSlice entries of the groups that are
 // split, sp.list[i] = {group, index among the split groups, begin, end}, and
 // sp.ctl [0] = split groups, [1] = slices.
@@ -650,7 +652,8 @@ __global__ void __launch_bounds__(kTailThreads) group_scan_kernel(const uint32_t
                                                                   const int64_t* __restrict__ counters,
                                                                   uint32_t* __restrict__ group_off,
                                                                   uint32_t* __restrict__ order, int64_t capacity,
-                                                                  GroupSplit sp) {
+                                                                  GroupSplit sp, const int64_t* stop,
+                                                                  uint32_t* __restrict__ bucket_count) {
     const int G = gm.G;
     // per-tile bin counts: each group's first segment, segment count and the
     // most sub-bins (up to SB) whose codes fit the group sort's counters
@@ -670,7 +673,8 @@ __global__ void __launch_bounds__(kTailThreads) group_scan_kernel(const uint32_t
     if (threadIdx.x < kClasses) chist[threadIdx.x] = 0;
     // consecutive groups per thread, as few as cover them
     const int per = (G + kTailThreads - 1) / kTailThreads, i0 = per * threadIdx.x;
-    const bool wrapped = (uint64_t)counters[0] >> 32 != 0;
+    const bool wrapped = (uint64_t)counters[0] >> 32 != 0, off = stop && counters[2] != 0;
+    if (off && threadIdx.x == 0) bucket_count[kBuckets] = 1;
     uint32_t v[8], s = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -749,7 +753,7 @@ __global__ void __launch_bounds__(kTailThreads) group_scan_kernel(const uint32_t
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-        if (j < per && i0 + j < G) order[atomicAdd(&cbase[v[j] ? __builtin_clz(v[j]) : 32], 1u)] = (uint32_t)(i0 + j);
+        if (j < per && i0 + j < G) order[atomicAdd(&cbase[v[j] ? __builtin_clz(v[j]) : 32], 1u)] = off ? 0xFFFFFFFFu : (uint32_t)(i0 + j);
 }
 
 #ifndef TGS_SORT_THREADS
@@ -919,7 +923,7 @@ __global__ void __launch_bounds__(kSortThreads, 4) group_sort_kernel(
     uint32_t* __restrict__ bin_off, uint32_t* __restrict__ lists, int64_t list_stride,
     uint32_t* __restrict__ bucket_count, const int64_t* __restrict__ counters, bool queue_all,
     uint8_t* __restrict__ repaired, RecordSink rs, uint32_t* __restrict__ queued, uint32_t* __restrict__ tile_count,
-    GroupSplit sp, const int64_t* __restrict__ stop) {
+    GroupSplit sp) {
     constexpr int NT = kSortThreads;
     constexpr int kMaxPer = kMaxGroupSegs / NT;
     constexpr uint32_t kNone = 0xFFFFFFFFu;
@@ -985,13 +989,13 @@ __global__ void __launch_bounds__(kSortThreads, 4) group_sort_kernel(
         return;
     }
     const int g = (int)order[blockIdx.x - sp.slice_grid];
+    if (g < 0) return;  // stopped
     const int64_t cap = capacity;
     const uint32_t lo = (uint32_t)min((int64_t)group_off[g], cap);
     const uint32_t hi = (uint32_t)min((int64_t)group_off[g + 1], cap);
     if (sp.list && split_group(hi - lo)) return;
     const GroupCodes gc = codes_of(gm, g, nseg);
     if (lo == hi) {  // an empty group: offsets only
-        if (stopped(stop)) return;  // (all groups are empty then)
         for (int c = threadIdx.x; c < gc.segs; c += NT) {
             bin_off[gc.sbase + c] = lo;
             if (repaired) repaired[gc.sbase + c] = 0;
@@ -1342,9 +1346,10 @@ hipError_t launch_repair_select(const uint32_t* bin_off, int64_t T, int K, float
 }
 
 hipError_t launch_group_scan(const uint32_t* gcount, GroupMap gm, const int64_t* counters, uint32_t* group_off,
-                             uint32_t* order, int64_t capacity, const GroupSplit& sp, hipStream_t s) {
+                             uint32_t* order, int64_t capacity, const GroupSplit& sp, const int64_t* stop,
+                             uint32_t* bucket_count, hipStream_t s) {
     hipLaunchKernelGGL(group_scan_kernel, dim3(1), dim3(kTailThreads), 0, s, gcount, gm, counters, group_off, order,
-                       capacity, sp);
+                       capacity, sp, stop, bucket_count);
     return hipGetLastError();
 }
 
@@ -1353,10 +1358,10 @@ hipError_t launch_group_sort(const uint64_t* tmp_pair, uint16_t* tmp_code, const
                              uint32_t* lists, int64_t list_stride, uint32_t* bucket_count,
                              const int64_t* counters, bool queue_all, uint8_t* repaired, RecordSink rs,
                              uint32_t* queued, uint32_t* tile_count, const GroupSplit& sp, uint16_t* part_tile,
-                             const int64_t* stop, hipStream_t s) {
+                             hipStream_t s) {
     hipLaunchKernelGGL(gm.tagged ? group_sort_kernel<true> : group_sort_kernel<false>, dim3((unsigned)(sp.slice_grid + gm.G)), dim3(kSortThreads), 0, s, tmp_pair,
                        tmp_code, group_off, order, zrange, gm, nseg, capacity, pairs, bin_off, lists, list_stride, bucket_count,
-                       counters, queue_all, repaired, rs, queued, tile_count, sp, stop);
+                       counters, queue_all, repaired, rs, queued, tile_count, sp);
     if (sp.list) {
         hipLaunchKernelGGL(gm.tagged ? group_split_kernel<true> : group_split_kernel<false>, dim3((unsigned)std::min(sp.max_slices, kSplitGrid)),
                            dim3(kSplitThreads), 0, s, tmp_pair, tmp_code, group_off, zrange, gm, nseg, capacity, pairs,
